@@ -165,13 +165,13 @@ int dedloc_reduce_shard(const void *const *peer_codes, const float *const *peer_
 
 /* Workspace for dedloc_lamb_step / dedloc_round (and the LARS
  * counterparts dedloc_lars_step / dedloc_round_lars) with this tensor table
- * (offsets: host, n_tensors+1): two fp64 partial sums per 2048-element tile,
- * one 8-byte word per tensor (its trust ratio, tagged for the call that
- * wrote it) and a counter that advances the tag on every call, graph
+ * (offsets: host, n_tensors+1): 16 bytes of fp64 partial sums per 2048
+ * elements, one 8-byte word per tensor (its trust ratio, tagged for the call
+ * that wrote it) and a counter that advances the tag on every call, graph
  * replays included.  Returns 0 for an invalid table.  Its contents need no
  * initialisation: a word left by an earlier call on the workspace never
  * carries the current tag, and other contents match it only by a 2^-32
- * chance per tensor.  Calls that share one workspace must not overlap in
+ * chance per word.  Calls that share one workspace must not overlap in
  * time. */
 size_t dedloc_lamb_workspace_bytes(uint64_t P, const uint64_t *offsets, uint32_t n_tensors);
 
@@ -441,12 +441,13 @@ int dedloc_profile_end(uint32_t n_kinds, double *total_ms, uint64_t *launches);
 int dedloc_kernel_kinds(void);
 const char *dedloc_kernel_name(int kind);
 
-/* Test hook of the LAMB and LARS steps and rounds.  Inside the pass that
- * applies the update, one workgroup per tensor computes the tensor's trust
- * ratio and publishes it; the others poll for it at most `polls` times
- * (default 4096), then compute it themselves, in the same order, so the
- * results are the same bits for every value (0: every workgroup computes
- * it).  Process-wide, read when a call is made; returns the previous value. */
+/* Test hook of the LAMB and LARS steps and rounds.  One workgroup per tensor
+ * forms the tensor's trust ratio and publishes it; the others poll for it at
+ * most `polls` times (default 4096; at most 512 where LAMB holds the
+ * parameters on chip meanwhile), then do without: they compute it
+ * themselves, in the same order, or leave the tensor to the pass that
+ * follows.  The results are the same bits for every value.  Process-wide,
+ * read when a call is made; returns the previous value. */
 uint32_t dedloc_test_trust_polls(uint32_t polls);
 
 #ifdef __cplusplus

@@ -221,12 +221,13 @@ int run_reduce(int32_t codec, const PeerList &pl, uint32_t lo, uint32_t hi, bool
     return DEDLOC_OK;
 }
 
-// LAMB tile table: tensors in launch chunks of at most kChunkTensors.
+// Work table of an optimizer: tensors in launch chunks of at most
+// kChunkTensors.
 struct Plan {
     std::vector<Chunk> chunks;
-    std::vector<uint32_t> chunk_tiles;
-    uint32_t n_tiles = 0;
-    size_t ws_partials = 0, ws_trust = 0, ws_epoch = 0, ws_total = 0;
+    bool one_pass = false;  // LAMB in one pass (else the two passes)
+    bool nt = false;        // the two passes' non-temporal form
+    size_t ws_part = 0, ws_trust = 0, ws_total = 0;
 };
 
 int check_tensors(uint64_t P, const uint64_t *off, uint32_t T) {
@@ -243,51 +244,70 @@ int check_tensors(uint64_t P, const uint64_t *off, uint32_t T) {
     return DEDLOC_OK;
 }
 
-void make_plan(uint64_t P, const uint64_t *off, const uint8_t *flags, uint32_t T, Plan &pl) {
-    (void)P;
+// LAMB's one pass (x and u held on chip until the tensor's ratio is known)
+// moves 28 instead of 40 bytes of state per element, but its persistent grid
+// and the wait for every tensor's ratio cost more than that saves on small
+// vectors and on tables of many small tensors.  Measured, one pass against
+// two: 2M elements in 20 tensors 21.0 / 19.2 us, 4M in one 28.7 / 30.6, 8M in
+// 20 49.9 / 55.7; 4M in 200 52 / 41, 9M in 300 138 / 122 (12 peers), 17.7M in
+// 25 98 / 123, 2^30 in 1024 8.7 / 10.3 ms (8 peers).
+constexpr uint64_t kOnePassElements = 1ull << 23;
+constexpr uint64_t kOnePassPerTensor = 1ull << 18;
+// The two passes' state beyond what the Infinity Cache keeps (x and v or m of
+// 2^23 elements are 64 MB of its 256): non-temporal accesses.
+constexpr uint64_t kNtElements = 1ull << 23;
+
+void make_plan(int opt, uint64_t P, const uint64_t *off, const uint8_t *flags, uint32_t T, Plan &pl) {
+    uint64_t full = 0;  // tensors with elements
+    for (uint32_t t = 0; t < T; t++) full += off[t + 1] > off[t];
+    pl.one_pass = opt == kOptLamb && P >= kOnePassElements && P / full >= kOnePassPerTensor;
+    pl.nt = P >= kNtElements;
+    const uint32_t per = pl.one_pass ? 2 : 1;  // rows per work item
     pl.chunks.clear();
-    pl.chunk_tiles.clear();
-    uint32_t base_tile = 0;
+    uint32_t all_rows = 0;
     uint32_t t0 = 0;
     while (t0 < T) {
         Chunk c;
         memset(&c, 0, sizeof c);
         c.base = off[t0];
         c.t0 = t0;
-        c.tile_base = base_tile;
-        uint32_t tiles = 0, k = 0;
+        c.row_base = all_rows;
+        uint32_t items = 0, odd = 0, k = 0;
         // take tensors while they fit the table and the chunk spans < 2^32 elements
         while (k < (uint32_t)kChunkTensors && t0 + k < T && off[t0 + k + 1] - c.base < (1ull << 32)) {
             c.start[k] = (uint32_t)(off[t0 + k] - c.base);
-            c.tile_begin[k] = tiles;
+            c.begin[k] = items;
+            c.odd_before[k] = (uint8_t)odd;
             c.flags[k] = flags ? flags[t0 + k] : 0;
-            const uint64_t len = off[t0 + k + 1] - off[t0 + k];
-            tiles += (uint32_t)((len + kTile - 1) / kTile);
+            const uint32_t rows = (uint32_t)((off[t0 + k + 1] - off[t0 + k] + kRow - 1) / kRow);
+            items += (rows + per - 1) / per;
+            odd += rows % 2;
+            all_rows += rows;
             k++;
         }
         if (k == 0) k = 1;  // unreachable: every tensor was checked to span < 2^32 elements
         c.nt = k;
         c.start[k] = (uint32_t)(off[t0 + k] - c.base);
-        c.tile_begin[k] = tiles;
+        c.begin[k] = items;
         pl.chunks.push_back(c);
-        pl.chunk_tiles.push_back(tiles);
-        base_tile += tiles;
         t0 += k;
     }
-    pl.n_tiles = base_tile;
-    pl.ws_partials = round_up((size_t)base_tile * 2 * sizeof(double), 256);
+    pl.ws_part = round_up((size_t)all_rows * 2 * sizeof(double), 256);
     pl.ws_trust = round_up((size_t)T * sizeof(unsigned long long), 256);
-    pl.ws_epoch = 256;
-    pl.ws_total = pl.ws_partials + pl.ws_trust + pl.ws_epoch;
+    pl.ws_total = 256 + pl.ws_part + pl.ws_trust;
 }
 
-LambWs carve(const Plan &pl, void *ws) {
+// The counter comes first: calls with different tables that take turns on
+// one workspace all advance the same one.
+LineWs carve_line(const Plan &pl, void *ws) {
     char *b = (char *)ws;
-    LambWs w;
-    w.partials = (double *)b;
-    w.trust = (unsigned long long *)(b + pl.ws_partials);
-    w.epoch = (uint32_t *)(b + pl.ws_partials + pl.ws_trust);
-    return w;
+    return {(uint32_t *)b, (uint32_t *)(b + 128), (unsigned long long *)(b + 256),
+            (unsigned long long *)(b + 256 + pl.ws_part)};
+}
+
+TileWs carve_tiles(const Plan &pl, void *ws) {
+    char *b = (char *)ws;
+    return {(double *)(b + 256), (unsigned long long *)(b + 256 + pl.ws_part), (uint32_t *)b};
 }
 
 // Polls of a tensor's published trust ratio in pass B before a workgroup
@@ -363,23 +383,67 @@ uint32_t next_nonce() {
     return ctr.fetch_add(0x9E3779B9u, std::memory_order_relaxed);
 }
 
-// Per chunk of tensors: pass A (gradient from src_a) and pass B, which
-// computes the trust ratios (LARS reads the gradient again from src_b).
-int run_opt(int opt, int src_a, int src_b, const Plan &pl, const PeerTable *pt, const GradArgs &ga_a,
-            const GradArgs &ga_b, const OptParams &op, float *x, float *m, float *v, void *ws,
+// Compute units of the current device (the persistent grid's size).
+uint32_t cu_count() {
+    static std::atomic<int> known[64];
+    int dev = 0, n = 0;
+    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return 256;
+    n = known[dev].load(std::memory_order_relaxed);
+    if (n == 0) {
+        if (hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n <= 0) n = 256;
+        known[dev].store(n, std::memory_order_relaxed);
+    }
+    return (uint32_t)n;
+}
+
+// Per chunk of tensors: pass A (gradient from src_a) and pass B (LARS reads
+// the gradient again from src_b).
+int run_opt(int opt, int src_a, int src_b, const Plan &pl, const PeerTable *peers, const GradArgs &ga_a,
+            const GradArgs &ga_b, const OptParams &op_in, float *x, float *m, float *v, void *ws,
             float *trust_out, hipStream_t s) {
-    const LambWs w = carve(pl, ws);
+    static const PeerTable no_peers = {};
+    const PeerTable &pt = peers ? *peers : no_peers;
     const int k_a = (opt == kOptLamb ? K_LAMB_A_F32 : K_LARS_A_F32) + std::min(src_a, (int)kSrcPeersFP16);
     const int k_b = opt == kOptLamb ? K_LAMB_B : K_LARS_B;
     const uint32_t nonce = next_nonce();
-    for (size_t c = 0; c < pl.chunks.size(); c++) {
-        const Chunk &ch = pl.chunks[c];
-        const uint32_t tiles = pl.chunk_tiles[c];
-        hipError_t e = timed(k_a, s, [&] { return launch_opt_a(opt, src_a, ch, tiles, pt, ga_a, op, x, m, v, w, s); });
-        if (e != hipSuccess) return hip_fail(e, "optimizer pass A launch");
-        e = timed(k_b, s, [&] {
-            return launch_opt_b(opt, src_b, ch, tiles, ga_b, op, x, m, v, w, nonce, trust_out, s);
-        });
+    OptParams op = op_in;
+    // One pass: a unit leaves the line kLineUnits turns after it entered, and
+    // the last unit of its tensor must have been taken a turn before that.
+    // A wait is then one for the sums (a few us); if other work on the GPU
+    // keeps part of the grid from running, it ends after about half a
+    // millisecond, and pass B does the rest.
+    const uint32_t cus = pl.one_pass ? cu_count() : 0, groups = cus * kLineGroups;
+    if (pl.one_pass) {
+        op.hold = (kLineUnits - 1) * groups;
+        op.trust_polls = std::min(op.trust_polls, 512u);
+    }
+    for (const Chunk &ch : pl.chunks) {
+        hipError_t e;
+        if (pl.one_pass) {
+            const LineWs w = carve_line(pl, ws);
+            const uint32_t units = ch.begin[ch.nt];
+            e = timed(k_a, s, [&] {
+                return launch_lamb_a(src_a, ch, std::min(units, groups), pt, ga_a, op, x, m, v, w, nonce, trust_out, s);
+            });
+            if (e != hipSuccess) return hip_fail(e, "optimizer pass A launch");
+            RestTable rt;
+            memset(&rt, 0, sizeof rt);
+            for (uint32_t k = 0; k < ch.nt; k++) {
+                const uint32_t n = ch.begin[k + 1] - ch.begin[k];
+                rt.begin[k] = rt.n_rest;
+                if (n > op.hold) rt.n_rest += 2 * (n - op.hold);
+            }
+            rt.begin[ch.nt] = rt.n_rest;
+            const uint32_t n_check = std::max(1u, std::min(cus, units));
+            e = timed(k_b, s, [&] { return launch_lamb_b(ch, rt, n_check, op, x, m, v, w, nonce, trust_out, s); });
+        } else {
+            const TileWs w = carve_tiles(pl, ws);
+            e = timed(k_a, s, [&] { return launch_opt_a(opt, src_a, pl.nt, ch, pt, ga_a, op, x, m, v, w, s); });
+            if (e != hipSuccess) return hip_fail(e, "optimizer pass A launch");
+            e = timed(k_b, s, [&] {
+                return launch_opt_b(opt, src_b, pl.nt, ch, ga_b, op, x, m, v, w, nonce, trust_out, s);
+            });
+        }
         if (e != hipSuccess) return hip_fail(e, "optimizer pass B launch");
     }
     return DEDLOC_OK;
@@ -394,7 +458,7 @@ int prepare_step(int opt, float *x, float *m, float *v, const void *grad, const 
     rc = check_tensors(P, offsets, n_tensors);
     if (rc) return rc;
     if (!flags) return fail(DEDLOC_ERR_INVALID_ARG, "flags must not be NULL");
-    make_plan(P, offsets, flags, n_tensors, pl);
+    make_plan(opt, P, offsets, flags, n_tensors, pl);
     rc = check_state(opt, x, m, v, P, ws, ws_bytes, pl);
     if (rc) return rc;
     if (P == 0) return DEDLOC_OK;
@@ -437,7 +501,7 @@ int prepare_round(int opt, const void *const *peer_codes, const float *const *pe
     rc = check_tensors(P, offsets, n_tensors);
     if (rc) return rc;
     if (!flags) return fail(DEDLOC_ERR_INVALID_ARG, "flags must not be NULL");
-    make_plan(P, offsets, flags, n_tensors, pl);
+    make_plan(opt, P, offsets, flags, n_tensors, pl);
     rc = check_state(opt, x, m, v, P, ws, ws_bytes, pl, check_ws);
     if (rc) return rc;
     if (P == 0) return DEDLOC_OK;
@@ -645,7 +709,7 @@ int dedloc_reduce_shard(const void *const *peer_codes, const float *const *peer_
 size_t dedloc_lamb_workspace_bytes(uint64_t P, const uint64_t *offsets, uint32_t n_tensors) {
     if (check_tensors(P, offsets, n_tensors)) return 0;
     Plan pl;
-    make_plan(P, offsets, nullptr, n_tensors, pl);
+    make_plan(kOptLamb, P, offsets, nullptr, n_tensors, pl);
     return pl.ws_total;
 }
 

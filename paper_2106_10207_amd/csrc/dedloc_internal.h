@@ -8,17 +8,11 @@
 namespace dedloc {
 
 // Launch-shape tuning (set from measurements on MI355X).
-#ifndef DEDLOC_VPL
-#define DEDLOC_VPL 1          // 8-element vectors per lane in a LAMB tile
-#endif
 #ifndef DEDLOC_PEER_BATCH
 #define DEDLOC_PEER_BATCH 16  // peer loads issued before the first fma
 #endif
 #ifndef DEDLOC_NT_PEERS
 #define DEDLOC_NT_PEERS 1     // non-temporal hint on loads of data read once
-#endif
-#ifndef DEDLOC_NT_STORES
-#define DEDLOC_NT_STORES 0    // non-temporal hint on streamed stores
 #endif
 #ifndef DEDLOC_NT_MSG_STORES
 #define DEDLOC_NT_MSG_STORES 1  // non-temporal hint on stores of encoded messages
@@ -29,16 +23,24 @@ namespace dedloc {
 #ifndef DEDLOC_I8_BATCH
 #define DEDLOC_I8_BATCH 16    // int8 peer messages loaded per batch in the reduce
 #endif
-#ifndef DEDLOC_B_REVERSE
-#define DEDLOC_B_REVERSE 1    // pass B visits tiles last-to-first (its re-reads
-                              // start with what pass A touched last)
-#endif
 
 constexpr int kWG = 256;               // threads per workgroup: 4 wave64
 constexpr int kVec = 8;                // fp32/fp16 elements per lane (16 B of fp16, 2x16 B of fp32)
-constexpr int kVPL = DEDLOC_VPL;
 constexpr int kPeerBatch = DEDLOC_PEER_BATCH;
-constexpr int kTile = kWG * kVec * kVPL;  // LAMB tile: elements of one tensor per workgroup
+constexpr int kRow = kWG * kVec;       // elements a workgroup works on at a time
+
+// LAMB in one pass: a persistent grid of kLineGroups workgroups per CU, each
+// holding kLineRegs rows in registers and kLineLds rows in LDS (16 KB a row)
+// until their tensor's trust ratio is known: 256 CUs hold 768 * 6 rows, 9.4M
+// elements.  More workgroups with shorter lines (4 per CU, 2 + 2 rows) and
+// fewer with longer ones (2 per CU, 6 + 4) were slower: ALBERT-xlarge's round
+// 978 against 1039 and 1081 us, ALBERT-large's 198 against 201 and 223.
+constexpr int kLineGroups = 3;
+constexpr int kLineRegs = 3;
+constexpr int kLineLds = 3;
+constexpr int kLineUnits = (kLineRegs + kLineLds) / 2;  // units (two rows) in a line
+// peer loads in flight per lane there (4, 8, 16: ALBERT-large with 16 peers 188, 199, 213 us)
+constexpr int kLinePeerBatch = 4;
 constexpr int kMaxPeers = 64;          // peer table lives in the kernel arguments
 constexpr int kI8Block = 1024;         // int8 codec block = one wave64 x 16 codes
 constexpr int kI8PerLane = 16;
@@ -87,18 +89,26 @@ struct ChainArgs {
     LocalArgs local;
 };
 
-// A run of consecutive tensors handled by one LAMB launch (it spans fewer
-// than 2^32 elements).  Tiles never cross a tensor: tensor k of the chunk
-// covers elements base + [start[k], start[k+1]) and owns launch blocks
-// [tile_begin[k], tile_begin[k+1]).
+// A run of consecutive tensors handled by one optimizer launch (it spans
+// fewer than 2^32 elements).  Work items (tiles of one row; units of two
+// in LAMB's one pass) never cross a tensor: tensor k of the chunk covers elements base +
+// [start[k], start[k+1]) and owns items [begin[k], begin[k+1]).
 struct Chunk {
-    uint64_t base;                        // absolute offset of the chunk's first element
-    uint32_t nt;                          // tensors in this chunk
-    uint32_t t0;                          // index of the chunk's first tensor
-    uint32_t tile_base;                   // index of the chunk's first tile in the workspace
-    uint32_t start[kChunkTensors + 1];    // element offsets relative to base
-    uint32_t tile_begin[kChunkTensors + 1];
+    uint64_t base;                      // absolute offset of the chunk's first element
+    uint32_t nt;                        // tensors in this chunk
+    uint32_t t0;                        // index of the chunk's first tensor
+    uint32_t row_base;                 // rows of the tensors before the chunk
+    uint32_t start[kChunkTensors + 1];  // element offsets relative to base
+    uint32_t begin[kChunkTensors + 1];
+    uint8_t odd_before[kChunkTensors];  // tensors of the chunk before k with an odd number of rows
     uint8_t flags[kChunkTensors];
+};
+
+// The rows of a chunk that LAMB's one pass does not hold on chip: tensor k
+// owns workgroups [begin[k], begin[k+1]) of the pass after it [begin[k], begin[k+1]).
+struct RestTable {
+    uint32_t begin[kChunkTensors + 1];
+    uint32_t n_rest;  // begin[nt]
 };
 
 // Optimizer applied after the gather.
@@ -113,7 +123,8 @@ struct OptParams {
     float beta1, beta2, omb1, omb2, c1, c2, eps;  // LAMB
     float momentum, trust_coef;                   // LARS
     int32_t unit_trust;
-    uint32_t trust_polls;  // pass B: polls of a tensor's published ratio before computing it
+    uint32_t trust_polls;  // polls for a tensor's published ratio before doing without it
+    uint32_t hold;         // LAMB's pass A holds the last so many units of every tensor on chip
 };
 
 // Where the LAMB step takes its gradient from.
@@ -136,10 +147,19 @@ struct GradArgs {
     LocalArgs local;         // kSrcPeersFP16Chain / kSrcPeersFP16Local
 };
 
-struct LambWs {
-    double *partials;            // 2 per tile: sum x^2, sum u^2
+struct TileWs {
+    double *partials;            // 2 per tile: sum x^2, sum u^2 (LARS: g^2)
     unsigned long long *trust;   // per tensor: (epoch << 32) | bits of r_t, published inside pass B
     uint32_t *epoch;             // the tag of the current launch: advanced by pass A, read by pass B
+};
+
+// Every word that another workgroup waits for carries the tag of the launch
+// that wrote it.
+struct LineWs {
+    uint32_t *epoch;             // [0]: read by pass A, advanced by pass B; [1]: pass A's value for pass B
+    uint32_t *gave_up;           // the tag if any tensor of the launch was given up
+    unsigned long long *part;    // 16 bytes per row: the partial sums
+    unsigned long long *trust;   // per tensor: (tag << 32) | bits of r_t
 };
 
 // Launchers (return hipError_t of the launch).
@@ -150,12 +170,15 @@ hipError_t launch_decode_i8(const int8_t *codes, const float *scales, uint64_t n
                             hipStream_t s);
 hipError_t launch_reduce_fp16(const GroupTable &gt, uint64_t len, const ChainArgs &ca, hipStream_t s);
 hipError_t launch_reduce_i8(const GroupTable &gt, uint64_t len, const ChainArgs &ca, hipStream_t s);
-hipError_t launch_opt_a(int opt, int src, const Chunk &ch, uint32_t n_tiles, const PeerTable *pt,
-                        const GradArgs &ga, const OptParams &op, float *x, float *m, float *v,
-                        const LambWs &ws, hipStream_t s);
-hipError_t launch_opt_b(int opt, int src, const Chunk &ch, uint32_t n_tiles, const GradArgs &ga,
-                        const OptParams &op, float *x, float *m, float *v, const LambWs &ws, uint32_t nonce,
-                        float *trust_out, hipStream_t s);
+hipError_t launch_lamb_a(int src, const Chunk &ch, uint32_t n_groups, const PeerTable &pt, const GradArgs &ga,
+                         const OptParams &op, float *x, float *m, float *v, const LineWs &ws, uint32_t nonce,
+                         float *trust_out, hipStream_t s);
+hipError_t launch_lamb_b(const Chunk &ch, const RestTable &rt, uint32_t n_check, const OptParams &op, float *x, float *m,
+                         float *v, const LineWs &ws, uint32_t nonce, float *trust_out, hipStream_t s);
+hipError_t launch_opt_a(int opt, int src, bool nt, const Chunk &ch, const PeerTable &p, const GradArgs &ga,
+                        const OptParams &op, float *x, float *m, float *v, const TileWs &ws, hipStream_t s);
+hipError_t launch_opt_b(int opt, int src, bool nt, const Chunk &ch, const GradArgs &ga, const OptParams &op, float *x,
+                        float *m, float *v, const TileWs &ws, uint32_t nonce, float *trust_out, hipStream_t s);
 hipError_t launch_accumulate(float *acc, const void *grad, bool fp16, uint64_t n, float b, hipStream_t s);
 hipError_t launch_finalize_fp16(float *acc, uint64_t n, float count, uint16_t *codes, int reset, hipStream_t s);
 hipError_t launch_finalize_i8(float *acc, uint64_t n, float count, int8_t *codes, float *scales, int reset,

@@ -20,16 +20,11 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 // ---------------------------------------------------------------- helpers
 
-// Loads of data read once (peer messages) and stores of data written once.
+// Loads of data read once (peer messages).
 template <typename T>
 __device__ __forceinline__ T ld_stream(const T *p) {
     if (DEDLOC_NT_PEERS) return __builtin_nontemporal_load(p);
     return *p;
-}
-template <typename T>
-__device__ __forceinline__ void st_stream(T *p, T v) {
-    if (DEDLOC_NT_STORES) __builtin_nontemporal_store(v, p);
-    else *p = v;
 }
 // Stores of encoded messages (read by other peers, not by this kernel).
 template <typename T>
@@ -276,7 +271,7 @@ __device__ __forceinline__ void init8(const float *acc_in, uint64_t e0, float *a
 
 // Eight consecutive fp16 elements starting at e0 (all in range), peers
 // [p_lo, p_hi) of the table, added to the running sums in acc.
-template <int B = kPeerBatch>  // peer loads kept in flight per lane
+template <int B>  // peer loads kept in flight per lane
 __device__ __forceinline__ void reduce_fp16x8(const PeerTable &pt, uint32_t p_lo, uint32_t p_hi,
                                               uint64_t e0, float *acc) {
     for (uint32_t p0 = p_lo; p0 < p_hi; p0 += B) {
@@ -309,10 +304,13 @@ __device__ __forceinline__ float reduce_fp16_one(const PeerTable &pt, uint32_t p
 // message and their decoded values averaged like any peer's.  (Issuing the
 // next peers' loads before the local peer's values are used measured the
 // same, and keeping the local loads inside a peer batch costs registers.)
+template <int B>
 __device__ __forceinline__ void reduce_fp16x8_local(const PeerTable &pt, uint32_t n, uint32_t lp,
                                                     const LocalArgs &la, uint64_t e0, float *acc) {
-    reduce_fp16x8(pt, 0, lp, e0, acc);
-    const f32x4 ga = ld_stream((const f32x4 *)(la.grad + e0)), gb = ld_stream((const f32x4 *)(la.grad + e0 + 4));
+    reduce_fp16x8<B>(pt, 0, lp, e0, acc);
+    // plain loads: the two halves of each 32 bytes would otherwise be fetched
+    // apart (ALBERT-large's round 207 instead of 198 us)
+    const f32x4 ga = *(const f32x4 *)(la.grad + e0), gb = *(const f32x4 *)(la.grad + e0 + 4);
     const float v[8] = {ga[0], ga[1], ga[2], ga[3], gb[0], gb[1], gb[2], gb[3]};
     const u32x4 lc = pack_fp16x8(v);
     st_msg((u32x4 *)((uint16_t *)la.codes + e0), lc);
@@ -321,7 +319,7 @@ __device__ __forceinline__ void reduce_fp16x8_local(const PeerTable &pt, uint32_
     const float w = pt.w[lp];
 #pragma unroll
     for (int i = 0; i < 8; i++) acc[i] = fmaf(w, d[i], acc[i]);
-    reduce_fp16x8(pt, lp + 1, n, e0, acc);
+    reduce_fp16x8<B>(pt, lp + 1, n, e0, acc);
 }
 
 __device__ __forceinline__ float reduce_fp16_one_local(const PeerTable &pt, uint32_t n, uint32_t lp,
@@ -349,7 +347,7 @@ __global__ __launch_bounds__(kWG) void reduce_fp16_kernel(const GroupTable gt, u
     if (e0 + kVec <= len) {
         float acc[8];
         init8(ca.acc_in, e0, acc);
-        if (local) reduce_fp16x8_local(gt.pt, p_hi, ca.local.pos, ca.local, e0, acc);
+        if (local) reduce_fp16x8_local<B>(gt.pt, p_hi, ca.local.pos, ca.local, e0, acc);
         else reduce_fp16x8<B>(gt.pt, p_lo, p_hi, e0, acc);
         if (ca.final_pass) *(u32x4 *)(out + e0) = pack_fp16x8(acc);
         if (mean) {
@@ -477,20 +475,20 @@ __device__ __forceinline__ float lamb_dir(float mn, float vn, float x, float lam
     return mh / (sqrtf(vh) + op.eps) + lam * x;
 }
 
-// Tensor of launch block b: the largest k with tile_begin[k] <= b (empty
-// tensors own no blocks and are skipped).  All values are wave-uniform.
+// Tensor of tile or unit b of a chunk: the largest k with begin[k] <= b (empty
+// tensors own none and are skipped).  All values are wave-uniform.
 __device__ __forceinline__ uint32_t chunk_tensor(const Chunk &ch, uint32_t b) {
     uint32_t lo = 0, hi = ch.nt;
     while (hi - lo > 1) {
         const uint32_t mid = (lo + hi) >> 1;
-        if (ch.tile_begin[mid] <= b) lo = mid;
+        if (ch.begin[mid] <= b) lo = mid;
         else hi = mid;
     }
     return lo;
 }
 
 // Gradient of the elements [e0, e0+cnt), cnt <= 8, for source SRC.
-template <int SRC>
+template <int SRC, int B>
 __device__ __forceinline__ void load_grad(const GradArgs &ga, const PeerTable &pt, uint64_t e0,
                                           int cnt, float *g) {
     if (cnt == kVec) {
@@ -509,8 +507,8 @@ __device__ __forceinline__ void load_grad(const GradArgs &ga, const PeerTable &p
         } else {
             float acc[8];
             init8(SRC == kSrcPeersFP16Chain ? ga.acc_in : nullptr, e0, acc);
-            if (SRC != kSrcPeersFP16 && ga.local.pos >= 0) reduce_fp16x8_local(pt, pt.n, ga.local.pos, ga.local, e0, acc);
-            else reduce_fp16x8(pt, 0, pt.n, e0, acc);
+            if (SRC != kSrcPeersFP16 && ga.local.pos >= 0) reduce_fp16x8_local<B>(pt, pt.n, ga.local.pos, ga.local, e0, acc);
+            else reduce_fp16x8<B>(pt, 0, pt.n, e0, acc);
             const u32x4 c = pack_fp16x8(acc);
             st_msg((u32x4 *)(ga.out_codes + e0), c);
             if (ga.out_mean) {
@@ -546,84 +544,118 @@ __device__ __forceinline__ void load_grad(const GradArgs &ga, const PeerTable &p
     }
 }
 
+// Eight elements per lane, of which cnt exist.  NT: non-temporal, for state
+// that is not read again before the caches have turned over.
+template <bool NT>
 __device__ __forceinline__ void load8(const float *p, uint64_t e0, int cnt, float *o) {
     if (cnt == kVec) {
-        const f32x4 a = *(const f32x4 *)(p + e0), b = *(const f32x4 *)(p + e0 + 4);
+        const f32x4 *q = (const f32x4 *)(p + e0);
+        const f32x4 a = NT ? __builtin_nontemporal_load(q) : q[0], b = NT ? __builtin_nontemporal_load(q + 1) : q[1];
         o[0] = a[0]; o[1] = a[1]; o[2] = a[2]; o[3] = a[3];
         o[4] = b[0]; o[5] = b[1]; o[6] = b[2]; o[7] = b[3];
     } else {
+#pragma unroll
         for (int j = 0; j < kVec; j++) o[j] = j < cnt ? p[e0 + j] : 0.0f;
     }
 }
 
+template <bool NT>
 __device__ __forceinline__ void store8(float *p, uint64_t e0, int cnt, const float *o) {
     if (cnt == kVec) {
-        st_stream((f32x4 *)(p + e0), f32x4{o[0], o[1], o[2], o[3]});
-        st_stream((f32x4 *)(p + e0 + 4), f32x4{o[4], o[5], o[6], o[7]});
+        f32x4 *q = (f32x4 *)(p + e0);
+        const f32x4 a = {o[0], o[1], o[2], o[3]}, b = {o[4], o[5], o[6], o[7]};
+        if (NT) {
+            __builtin_nontemporal_store(a, q);
+            __builtin_nontemporal_store(b, q + 1);
+        } else {
+            q[0] = a;
+            q[1] = b;
+        }
     } else {
-        for (int j = 0; j < cnt; j++) p[e0 + j] = o[j];
+#pragma unroll
+        for (int j = 0; j < kVec; j++)
+            if (j < cnt) p[e0 + j] = o[j];
     }
 }
 
-// Pass A.  LAMB: gradient (optionally the fused average), new moments, and
-// the per-tile sums of x^2 and u^2.  LARS: gradient (optionally the fused
-// average) and the per-tile sums of x^2 and g^2; nothing else is written.
-// Sums are fp64 with a fixed tree inside the tile.
-template <int SRC, int OPT>
-__global__ __launch_bounds__(kWG) void opt_a_kernel(const Chunk ch, const PeerTable pt,
-                                                    const GradArgs ga, const OptParams op,
-                                                    const float *__restrict__ x,
-                                                    float *__restrict__ m, float *__restrict__ v,
-                                                    LambWs ws) {
+__device__ __forceinline__ int count8(uint64_t e0, uint64_t t_hi) {
+    return e0 >= t_hi ? 0 : (int)(t_hi - e0 < (uint64_t)kVec ? t_hi - e0 : (uint64_t)kVec);
+}
+
+// The ratio of a tensor from its sums (r = 1 when disabled or a norm is 0).
+//   LAMB: r = ||x|| / ||u||;  LARS: r = eta*||x|| / (||g|| + lambda*||x||).
+template <int OPT>
+__device__ __forceinline__ float trust_ratio(uint8_t flags, const OptParams &op, double a0, double a1) {
+    const double X = sqrt(a0), Y = sqrt(a1);
+    float r = 1.0f;
+    if (!op.unit_trust && (flags & 2u) && X > 0.0 && Y > 0.0) {
+        if (OPT == kOptLamb) {
+            r = (float)(X / Y);
+        } else {
+            const double lam = (flags & 1u) ? (double)op.wd : 0.0;
+            r = (float)((double)op.trust_coef * X / (Y + lam * X));
+        }
+    }
+    return r;
+}
+
+// --------------------------------------------- the optimizer in two passes
+// Pass A: gradient (optionally the fused average), for LAMB the new moments,
+// and the per-tile sums of x^2 and u^2 (LARS: g^2), in fp64 with a fixed tree
+// inside the tile; pass B: the ratios and the update, from memory again.
+// NT: non-temporal accesses for the state that no other pass of the call
+// reads again, for vectors that the 256 MB Infinity Cache does not keep from
+// one call to the next (ResNet-50, 32 peers, LARS: 419 -> 406 us; on 6M
+// elements, which it keeps, 31.2 -> 33.6 us: the caller chooses by size).
+template <int SRC, int OPT, bool NT>
+__global__ __launch_bounds__(kWG) void opt_a_kernel(const Chunk ch, const PeerTable pt, const GradArgs ga,
+                                                    const OptParams op, const float *__restrict__ x,
+                                                    float *__restrict__ m, float *__restrict__ v, TileWs ws) {
     const uint32_t b = blockIdx.x;
     const uint32_t k = chunk_tensor(ch, b);
     const uint64_t t_lo = ch.base + ch.start[k], t_hi = ch.base + ch.start[k + 1];
-    const uint32_t tile = b - ch.tile_begin[k];
+    const uint32_t tile = b - ch.begin[k];
     const float lam = (ch.flags[k] & 1u) ? op.wd : 0.0f;
-
     double s0 = 0.0, s1 = 0.0;
+    const uint64_t e0 = t_lo + (uint64_t)tile * kRow + threadIdx.x * kVec;
+    const int cnt = count8(e0, t_hi);
+    if (cnt > 0) {
+        float g[8], xv[8];
+        load8<false>(x, e0, cnt, xv);
+        if (OPT == kOptLamb) {
+            float mv[8], vv[8];
+            load8<NT>(m, e0, cnt, mv);
+            load8<NT>(v, e0, cnt, vv);
+            load_grad<SRC, kPeerBatch>(ga, pt, e0, cnt, g);
 #pragma unroll
-    for (int r = 0; r < kVPL; r++) {
-        const uint64_t e0 = t_lo + (uint64_t)tile * kTile + ((uint64_t)r * kWG + threadIdx.x) * kVec;
-        if (e0 < t_hi) {
-            const int cnt = (int)(t_hi - e0 < (uint64_t)kVec ? t_hi - e0 : (uint64_t)kVec);
-            float g[8], xv[8];
-            load8(x, e0, cnt, xv);
-            if (OPT == kOptLamb) {
-                float mv[8], vv[8];
-                load8(m, e0, cnt, mv);
-                load8(v, e0, cnt, vv);
-                load_grad<SRC>(ga, pt, e0, cnt, g);
-#pragma unroll
-                for (int j = 0; j < 8; j++) {
-                    const float mn = fmaf(op.beta1, mv[j], op.omb1 * g[j]);
-                    const float vn = fmaf(op.beta2, vv[j], op.omb2 * (g[j] * g[j]));
-                    const float u = lamb_dir(mn, vn, xv[j], lam, op);
-                    mv[j] = mn;
-                    vv[j] = vn;
-                    if (j < cnt) {
-                        s0 += (double)xv[j] * (double)xv[j];
-                        s1 += (double)u * (double)u;
-                    }
+            for (int j = 0; j < 8; j++) {
+                const float mn = fmaf(op.beta1, mv[j], op.omb1 * g[j]);
+                const float vn = fmaf(op.beta2, vv[j], op.omb2 * (g[j] * g[j]));
+                const float u = lamb_dir(mn, vn, xv[j], lam, op);
+                mv[j] = mn;
+                vv[j] = vn;
+                if (j < cnt) {
+                    s0 += (double)xv[j] * (double)xv[j];
+                    s1 += (double)u * (double)u;
                 }
-                store8(m, e0, cnt, mv);
-                store8(v, e0, cnt, vv);
-            } else {
-                load_grad<SRC>(ga, pt, e0, cnt, g);
+            }
+            store8<false>(m, e0, cnt, mv);
+            store8<false>(v, e0, cnt, vv);
+        } else {
+            load_grad<SRC, kPeerBatch>(ga, pt, e0, cnt, g);
 #pragma unroll
-                for (int j = 0; j < 8; j++) {
-                    if (j < cnt) {
-                        s0 += (double)xv[j] * (double)xv[j];
-                        s1 += (double)g[j] * (double)g[j];
-                    }
+            for (int j = 0; j < 8; j++) {
+                if (j < cnt) {
+                    s0 += (double)xv[j] * (double)xv[j];
+                    s1 += (double)g[j] * (double)g[j];
                 }
             }
         }
     }
     block_sum2(s0, s1);
     if (threadIdx.x == 0) {
-        ws.partials[2 * (ch.tile_base + b)] = s0;
-        ws.partials[2 * (ch.tile_base + b) + 1] = s1;
+        ws.partials[2 * (uint64_t)(ch.row_base + b)] = s0;
+        ws.partials[2 * (uint64_t)(ch.row_base + b) + 1] = s1;
         // a fresh tag for the ratios pass B publishes (the only access to
         // this word during the launch; pass B reads it after the launch)
         if (b == 0) ws.epoch[0] = ws.epoch[0] + 1u;
@@ -633,9 +665,9 @@ __global__ __launch_bounds__(kWG) void opt_a_kernel(const Chunk ch, const PeerTa
 // Sums over tensor k of the chunk of its tile partials (x^2, and u^2 or
 // g^2), in a fixed order: lane-strided, then a fixed tree.  Every thread of
 // the workgroup calls it; thread 0 gets the sums.
-__device__ __forceinline__ void tensor_sums(const Chunk &ch, const LambWs &ws, uint32_t k, double &a0, double &a1) {
-    const uint32_t first = ch.tile_base + ch.tile_begin[k];
-    const uint32_t ntiles = ch.tile_begin[k + 1] - ch.tile_begin[k];
+__device__ __forceinline__ void tensor_sums(const Chunk &ch, const TileWs &ws, uint32_t k, double &a0, double &a1) {
+    const uint32_t first = ch.row_base + ch.begin[k];
+    const uint32_t ntiles = ch.begin[k + 1] - ch.begin[k];
     typedef double f64x2 __attribute__((ext_vector_type(2)));
     const f64x2 *part = (const f64x2 *)ws.partials + first;
     a0 = 0.0;
@@ -657,24 +689,6 @@ __device__ __forceinline__ void tensor_sums(const Chunk &ch, const LambWs &ws, u
     block_sum2(a0, a1);
 }
 
-// The ratio of tensor k from its sums (r = 1 when disabled or a norm is 0).
-//   LAMB: r = ||x|| / ||u||;  LARS: r = eta*||x|| / (||g|| + lambda*||x||).
-template <int OPT>
-__device__ __forceinline__ float trust_ratio(const Chunk &ch, const OptParams &op, uint32_t k, double a0,
-                                             double a1) {
-    const double X = sqrt(a0), Y = sqrt(a1);
-    float r = 1.0f;
-    if (!op.unit_trust && (ch.flags[k] & 2u) && X > 0.0 && Y > 0.0) {
-        if (OPT == kOptLamb) {
-            r = (float)(X / Y);
-        } else {
-            const double lam = (ch.flags[k] & 1u) ? (double)op.wd : 0.0;
-            r = (float)((double)op.trust_coef * X / (Y + lam * X));
-        }
-    }
-    return r;
-}
-
 // The trust ratio of tensor k inside pass B.  One workgroup of the tensor,
 // the producer (dispatched ahead of every other tile), sums the partials
 // and publishes r in the tensor's workspace word as (epoch << 32 | bits of
@@ -689,7 +703,7 @@ __device__ __forceinline__ float trust_ratio(const Chunk &ch, const OptParams &o
 // sums the partials itself, in the same order, so r is the same bits on
 // every path and every kernel exits.  Every thread calls it.
 template <int OPT>
-__device__ __forceinline__ float tensor_ratio(const Chunk &ch, const OptParams &op, const LambWs &ws,
+__device__ __forceinline__ float tensor_ratio(const Chunk &ch, const OptParams &op, const TileWs &ws,
                                               uint32_t k, bool producer, uint32_t epoch,
                                               float *__restrict__ trust_out) {
     __shared__ float s_r;
@@ -717,7 +731,7 @@ __device__ __forceinline__ float tensor_ratio(const Chunk &ch, const OptParams &
     double a0, a1;
     tensor_sums(ch, ws, k, a0, a1);
     if (threadIdx.x == 0) {
-        const float r = trust_ratio<OPT>(ch, op, k, a0, a1);
+        const float r = trust_ratio<OPT>(ch.flags[k], op, a0, a1);
         if (producer) {
             __hip_atomic_store(word, ((unsigned long long)epoch << 32) | __float_as_uint(r), __ATOMIC_RELAXED,
                                __HIP_MEMORY_SCOPE_AGENT);
@@ -733,76 +747,555 @@ __device__ __forceinline__ float tensor_ratio(const Chunk &ch, const OptParams &
 // the same operations as pass A.  LARS: v' = fma(mu, v, (lr*r_t)*(g + lambda*x)),
 // x' = x - v', with g read again from the gathered message (SRC).  The
 // tile's data are loaded and the step direction formed before r_t is known.
-template <int SRC, int OPT>
-__global__ __launch_bounds__(kWG) void opt_b_kernel(const Chunk ch, const GradArgs ga,
-                                                    const OptParams op, float *__restrict__ x,
-                                                    float *__restrict__ m, float *__restrict__ v,
-                                                    LambWs ws, uint32_t nonce, float *__restrict__ trust_out) {
+template <int SRC, int OPT, bool NT>
+__global__ __launch_bounds__(kWG) void opt_b_kernel(const Chunk ch, const GradArgs ga, const OptParams op,
+                                                    float *__restrict__ x, float *__restrict__ m,
+                                                    float *__restrict__ v, TileWs ws, uint32_t nonce,
+                                                    float *__restrict__ trust_out) {
     // Workgroups [0, nt) are the producers: tile 0 of tensor k = blockIdx.x
     // (the producer of an empty tensor writes r = 1 and exits).  The rest
-    // cover every tile b of the chunk (last to first when DEDLOC_B_REVERSE:
-    // the re-reads start with what pass A touched last) and skip tile 0.
+    // cover every tile b of the chunk, last to first (the re-reads start with
+    // what pass A touched last), and skip tile 0.
     uint32_t k, tile;
     const bool producer = blockIdx.x < ch.nt;
     if (producer) {
         k = blockIdx.x;
         tile = 0;
-        if (ch.tile_begin[k] == ch.tile_begin[k + 1]) {
+        if (ch.begin[k] == ch.begin[k + 1]) {
             if (threadIdx.x == 0 && trust_out) trust_out[ch.t0 + k] = 1.0f;
             return;
         }
     } else {
-        const uint32_t q = blockIdx.x - ch.nt;
-        const uint32_t b = DEDLOC_B_REVERSE ? gridDim.x - 1 - ch.nt - q : q;
+        const uint32_t b = gridDim.x - 1 - blockIdx.x;
         k = chunk_tensor(ch, b);
-        tile = b - ch.tile_begin[k];
+        tile = b - ch.begin[k];
         if (tile == 0) return;
     }
     const uint64_t t_hi = ch.base + ch.start[k + 1];
-    const uint64_t base = ch.base + ch.start[k] + (uint64_t)tile * kTile;
     const float lam = (ch.flags[k] & 1u) ? op.wd : 0.0f;
     const uint32_t epoch = ws.epoch[0] + nonce;  // ws.epoch: advanced by this chunk's pass A
     // the producer publishes r_t before touching its own tile (its partial
     // loads would otherwise queue behind the tile's loads)
     float lrr = producer ? op.lr * tensor_ratio<OPT>(ch, op, ws, k, true, epoch, trust_out) : 0.0f;
-    float xv[kVPL][8], dv[kVPL][8], vv[kVPL][8];
-    int cnt[kVPL];
-#pragma unroll
-    for (int r = 0; r < kVPL; r++) {
-        const uint64_t e0 = base + ((uint64_t)r * kWG + threadIdx.x) * kVec;
-        cnt[r] = e0 < t_hi ? (int)(t_hi - e0 < (uint64_t)kVec ? t_hi - e0 : (uint64_t)kVec) : 0;
-        if (cnt[r] == 0) continue;
-        load8(x, e0, cnt[r], xv[r]);
-        load8(v, e0, cnt[r], vv[r]);
+    const uint64_t e0 = ch.base + ch.start[k] + (uint64_t)tile * kRow + threadIdx.x * kVec;
+    const int cnt = count8(e0, t_hi);
+    float xv[8], dv[8], vv[8];
+    if (cnt > 0) {
+        load8<NT>(x, e0, cnt, xv);
+        load8<NT>(v, e0, cnt, vv);
         if (OPT == kOptLamb) {
             float mv[8];
-            load8(m, e0, cnt[r], mv);
+            load8<NT>(m, e0, cnt, mv);
 #pragma unroll
-            for (int j = 0; j < 8; j++) dv[r][j] = lamb_dir(mv[j], vv[r][j], xv[r][j], lam, op);
+            for (int j = 0; j < 8; j++) dv[j] = lamb_dir(mv[j], vv[j], xv[j], lam, op);
         } else {
             float g[8];
-            load_grad<SRC>(ga, PeerTable{}, e0, cnt[r], g);
+            load_grad<SRC, kPeerBatch>(ga, PeerTable{}, e0, cnt, g);
 #pragma unroll
-            for (int j = 0; j < 8; j++) dv[r][j] = g[j] + lam * xv[r][j];
+            for (int j = 0; j < 8; j++) dv[j] = g[j] + lam * xv[j];
         }
     }
     if (!producer) lrr = op.lr * tensor_ratio<OPT>(ch, op, ws, k, false, epoch, trust_out);
-#pragma unroll
-    for (int r = 0; r < kVPL; r++) {
-        if (cnt[r] == 0) continue;
-        const uint64_t e0 = base + ((uint64_t)r * kWG + threadIdx.x) * kVec;
+    if (cnt > 0) {
         if (OPT == kOptLamb) {
 #pragma unroll
-            for (int j = 0; j < 8; j++) xv[r][j] = xv[r][j] - lrr * dv[r][j];
+            for (int j = 0; j < 8; j++) xv[j] = xv[j] - lrr * dv[j];
         } else {
 #pragma unroll
             for (int j = 0; j < 8; j++) {
-                vv[r][j] = fmaf(op.momentum, vv[r][j], lrr * dv[r][j]);
-                xv[r][j] = xv[r][j] - vv[r][j];
+                vv[j] = fmaf(op.momentum, vv[j], lrr * dv[j]);
+                xv[j] = xv[j] - vv[j];
             }
-            store8(v, e0, cnt[r], vv[r]);
+            store8<NT>(v, e0, cnt, vv);
         }
-        store8(x, e0, cnt[r], xv[r]);
+        store8<NT>(x, e0, cnt, xv);
+    }
+}
+
+// ------------------------------------------------------ LAMB in one pass
+
+// Lane layout of LAMB's rows of 2048 elements, of which a wave works on 512.
+// GF: lane l holds elements 4l..4l+3 and 256+4l..256+4l+3 of its wave's 512,
+// so that every 16-byte access of the wave covers 1 KB without gaps.  With eight consecutive elements per lane (two accesses at a
+// 32-byte stride) a stream of 16 bytes read and 12 written per element ran at
+// 5.2 TB/s, with or without non-temporal hints; without gaps and with both
+// hints it runs at 5.7 to 6.0 TB/s (17.7M and 268M elements).
+__device__ __forceinline__ uint32_t row_at(int h) {
+    return (threadIdx.x & ~63u) * kVec + 256 * h + 4 * (threadIdx.x & 63);
+}
+
+// The fused average keeps eight consecutive elements per lane, which its
+// 16-byte message accesses need.
+template <bool GF>
+struct Row {
+    uint64_t row, t_hi;
+    __device__ __forceinline__ Row(uint64_t row_, uint64_t t_hi_) : row(row_), t_hi(t_hi_) {}
+    __device__ __forceinline__ bool full() const { return row + kRow <= t_hi; }  // workgroup-uniform
+    __device__ __forceinline__ uint64_t e0() const { return row + threadIdx.x * kVec; }
+    // whether the lane's element j (0..7) lies in the tensor
+    __device__ __forceinline__ bool has(int j) const {
+        return GF ? row + row_at(j >> 2) + (j & 3) < t_hi : e0() + j < t_hi;
+    }
+    // the lane's eight elements (zero past the end)
+    __device__ __forceinline__ void load(const float *__restrict__ p, float *o) const {
+        if (!GF) {
+            load8<true>(p, e0(), count8(e0(), t_hi), o);
+        } else if (full()) {
+#pragma unroll
+            for (int h = 0; h < 2; h++) {
+                const f32x4 a = __builtin_nontemporal_load((const f32x4 *)(p + row + row_at(h)));
+#pragma unroll
+                for (int j = 0; j < 4; j++) o[4 * h + j] = a[j];
+            }
+        } else {
+#pragma unroll
+            for (int j = 0; j < 8; j++) o[j] = has(j) ? p[row + row_at(j >> 2) + (j & 3)] : 0.0f;
+        }
+    }
+    __device__ __forceinline__ void store(float *__restrict__ p, const float *o) const {
+        if (!GF) {
+            store8<true>(p, e0(), count8(e0(), t_hi), o);
+        } else if (full()) {
+#pragma unroll
+            for (int h = 0; h < 2; h++)
+                __builtin_nontemporal_store(f32x4{o[4 * h], o[4 * h + 1], o[4 * h + 2], o[4 * h + 3]},
+                                            (f32x4 *)(p + row + row_at(h)));
+        } else {
+#pragma unroll
+            for (int j = 0; j < 8; j++)
+                if (has(j)) p[row + row_at(j >> 2) + (j & 3)] = o[j];
+        }
+    }
+};
+
+// The gradient of a row from a message (or an fp32 gradient) as loaded, so
+// that the loads can be in flight while another row is worked on.
+template <int SRC>
+struct RawGrad {
+    float g[SRC == kSrcF32 ? 8 : 1];
+    u32x4 c;     // fp16: the lane's eight codes; int8: two words of four
+    float s[2];  // int8: the block scales of the two words
+    __device__ __forceinline__ void load(const GradArgs &ga, const Row<true> &r) {
+        const uint64_t row = r.row;
+        if (SRC == kSrcF32) {
+            r.load((const float *)ga.grad, g);
+        } else if (SRC == kSrcFP16) {
+            const uint16_t *p = (const uint16_t *)ga.grad;
+            if (r.full()) {
+                const u32x2 a = ld_stream((const u32x2 *)(p + row + row_at(0)));
+                const u32x2 b = ld_stream((const u32x2 *)(p + row + row_at(1)));
+                c = u32x4{a[0], a[1], b[0], b[1]};
+            } else {
+                c = u32x4{0u, 0u, 0u, 0u};
+#pragma unroll
+                for (int j = 0; j < 8; j++)
+                    if (r.has(j)) c[j >> 1] |= (unsigned)p[row + row_at(j >> 2) + (j & 3)] << (16 * (j & 1));
+            }
+        } else if (SRC == kSrcI8) {
+            const int8_t *p = (const int8_t *)ga.grad;
+#pragma unroll
+            for (int h = 0; h < 2; h++) {  // rows start at multiples of 8: four codes share a block
+                const uint64_t e = row + row_at(h);
+                if (r.full()) {
+                    c[h] = ld_stream((const unsigned *)(p + e));
+                    s[h] = ga.scales[e / kI8Block];
+                } else {
+                    c[h] = 0u;
+                    s[h] = e < r.t_hi ? ga.scales[e / kI8Block] : 0.0f;
+#pragma unroll
+                    for (int j = 0; j < 4; j++)
+                        if (e + j < r.t_hi) c[h] |= (unsigned)(uint8_t)p[e + j] << (8 * j);
+                }
+            }
+        }
+    }
+    __device__ __forceinline__ void decode(float *o) const {
+        if (SRC == kSrcF32) {
+#pragma unroll
+            for (int j = 0; j < 8; j++) o[j] = g[j];
+        } else if (SRC == kSrcFP16) {
+            unpack_fp16x8(c, o);
+        } else if (SRC == kSrcI8) {
+#pragma unroll
+            for (int j = 0; j < 8; j++) o[j] = sbyte(c[j >> 2], j & 3) * s[j >> 2];
+        }
+    }
+};
+
+// Partial sums of a unit (x^2 and u^2) as four words, each half of a
+// double under the call's tag: whoever reads a word sees from it alone
+// whether this launch wrote it, so no ordering between two locations (a
+// release fence: on gfx950 a full L2 write-back) is needed.
+__device__ __forceinline__ void put_part(unsigned long long *w, uint32_t tag, double a, double b) {
+    const unsigned long long t = (unsigned long long)tag << 32;
+    const unsigned long long ab = (unsigned long long)__double_as_longlong(a);
+    const unsigned long long bb = (unsigned long long)__double_as_longlong(b);
+    __hip_atomic_store(w, t | (ab & 0xffffffffull), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_store(w + 1, t | (ab >> 32), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_store(w + 2, t | (bb & 0xffffffffull), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_store(w + 3, t | (bb >> 32), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// A unit's sums, and whether all four words carry the tag.
+__device__ __forceinline__ bool get_part(const unsigned long long *w, uint32_t tag, double &a, double &b) {
+    unsigned long long q[4];
+#pragma unroll
+    for (int i = 0; i < 4; i++) q[i] = __hip_atomic_load(w + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    a = __longlong_as_double((long long)((q[1] << 32) | (q[0] & 0xffffffffull)));
+    b = __longlong_as_double((long long)((q[3] << 32) | (q[2] & 0xffffffffull)));
+    return (uint32_t)(q[0] >> 32) == tag && (uint32_t)(q[1] >> 32) == tag && (uint32_t)(q[2] >> 32) == tag &&
+           (uint32_t)(q[3] >> 32) == tag;
+}
+
+__device__ __forceinline__ bool gave_up(const LineWs &ws, uint32_t tag) {
+    return __hip_atomic_load(ws.gave_up, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == tag;
+}
+
+// The same, polling at most `polls` times more, and less once any tensor of
+// the launch was given up.
+__device__ __forceinline__ bool wait_part(const LineWs &ws, const unsigned long long *w, uint32_t tag, uint32_t polls,
+                                          double &a, double &b) {
+    for (uint32_t i = 0; i < polls; i++) {
+        if (get_part(w, tag, a, b)) return true;
+        if (i % 16 == 15 && gave_up(ws, tag)) break;
+        __builtin_amdgcn_s_sleep(4);
+    }
+    return false;
+}
+
+// Sums over a tensor of the partials of its first n units (records from
+// `part` on), by the whole workgroup, in a fixed order: thread-strided, then
+// a fixed tree.  WAIT: poll for records not yet written (bounded); otherwise
+// all of them are there.  Returns whether every record was seen; thread 0
+// gets the sums.
+template <bool WAIT>
+__device__ __forceinline__ bool unit_sums(const LineWs &ws, const unsigned long long *part, uint32_t n, uint32_t tag,
+                                          uint32_t polls, double &a0, double &a1) {
+    bool ok = true;
+    a0 = 0.0;
+    a1 = 0.0;
+    for (uint32_t i = threadIdx.x; i < n && ok; i += kWG) {
+        double p, q;
+        if (WAIT) ok = wait_part(ws, part + 4 * (uint64_t)i, tag, polls, p, q);
+        else get_part(part + 4 * (uint64_t)i, tag, p, q);
+        a0 += p;
+        a1 += q;
+    }
+    const bool all = !WAIT || __syncthreads_and(ok);
+    block_sum2(a0, a1);
+    return all;
+}
+
+// Unit b of the chunk: two rows of one tensor (the tensor's last unit may
+// have one, and end within a row).
+struct UnitAt {
+    uint32_t k, unit, units;
+    uint64_t row, t_hi;  // first element, end of the tensor
+    // hint: a tensor that may well be it
+    __device__ __forceinline__ UnitAt(const Chunk &ch, uint32_t b, uint32_t hint) {
+        k = ch.begin[hint] <= b && b < ch.begin[hint + 1] ? hint : chunk_tensor(ch, b);
+        unit = b - ch.begin[k];
+        units = ch.begin[k + 1] - ch.begin[k];
+        row = ch.base + ch.start[k] + (uint64_t)unit * (2 * kRow);
+        t_hi = ch.base + ch.start[k + 1];
+    }
+    // Kept on chip until its tensor's ratio is known.
+    __device__ __forceinline__ bool held(const OptParams &op) const { return units - 1 - unit < op.hold; }
+};
+
+// The partials of tensor k: 16 bytes of workspace per row, which hold a
+// record of 32 bytes for every unit but the last, and the last one's two sums
+// untagged (the workgroup that owns it forms the ratio; pass B reads them
+// after the launch).
+__device__ __forceinline__ unsigned long long *tensor_parts(const Chunk &ch, const LineWs &ws, uint32_t k) {
+    return ws.part + 2 * (uint64_t)(ch.row_base + 2 * ch.begin[k] - ch.odd_before[k]);
+}
+
+// The word of a tensor decides for all of it: (tag << 32) | bits of r once
+// the ratio is known, or (tag << 32) | kFailed if a workgroup stopped waiting
+// for it first; whichever is swapped in first stays.  Every wait is bounded,
+// so every workgroup exits, whatever else runs on the GPU.
+constexpr uint32_t kFailed = 0xffffffffu;  // no r: its only NaN is the canonical one
+
+// Swap `low` in unless the word is decided already; returns what it holds.
+__device__ __forceinline__ uint32_t decide(unsigned long long *word, unsigned long long seen, uint32_t tag, uint32_t low) {
+    while ((uint32_t)(seen >> 32) != tag) {
+        if (__hip_atomic_compare_exchange_strong(word, &seen, ((unsigned long long)tag << 32) | low, __ATOMIC_RELAXED,
+                                                 __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
+            return low;
+    }
+    return (uint32_t)seen;
+}
+
+// Wait for the word's decision (`seen`: its content when last looked at).
+__device__ __forceinline__ uint32_t await_ratio(const LineWs &ws, const OptParams &op, unsigned long long *word,
+                                                unsigned long long seen, uint32_t tag) {
+    for (uint32_t i = 0; i < op.trust_polls && (uint32_t)(seen >> 32) != tag; i++) {
+        if (i % 16 == 15 && gave_up(ws, tag)) break;
+        __builtin_amdgcn_s_sleep(4);
+        seen = __hip_atomic_load(word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    if ((uint32_t)(seen >> 32) == tag) return (uint32_t)seen;
+    const uint32_t got = decide(word, seen, tag, kFailed);
+    if (got == kFailed) __hip_atomic_store(ws.gave_up, tag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    return got;
+}
+
+// LAMB in one pass: per row the gradient (optionally the fused average), the
+// new moments, and the sums of x^2 and u^2.  x and u then wait on chip, in a
+// line of NR register slots and NL LDS slots (rows) per workgroup, until the
+// tensor's trust ratio is known, and x' = x - (lr*r_t)*u is written.  The grid
+// is persistent: workgroup w takes units w, w + gridDim.x, ...
+template <int SRC>
+__global__ __launch_bounds__(kWG, kLineGroups) void lamb_a_kernel(const Chunk ch, const PeerTable pt,
+                                                          const GradArgs ga, const OptParams op,
+                                                          float *__restrict__ x,
+                                                          float *__restrict__ m, float *__restrict__ v,
+                                                          LineWs ws, uint32_t nonce, float *__restrict__ trust_out) {
+    constexpr uint32_t NR = kLineRegs, NL = kLineLds, S = NR + NL;
+    constexpr bool kPeers = SRC >= kSrcPeersFP16, GF = !kPeers;
+    __shared__ f32x4 park[4 * NL][kWG];
+    const uint32_t G = gridDim.x, n = ch.begin[ch.nt];
+    const uint32_t epoch = ws.epoch[0];
+    const uint32_t tag = epoch + nonce;
+    // the tag as pass B reads it (ws.epoch[0] is advanced there, and read
+    // here only)
+    if (blockIdx.x == 0 && threadIdx.x == 0) ws.epoch[1] = epoch;
+
+    float xr[NR][8], dr[NR][8];
+    uint32_t slot = 0, it = 0;  // slot: (it - NR) % NL
+    auto unpark = [&](uint32_t sl, float *xp, float *dp) {
+#pragma unroll
+        for (int q = 0; q < 2; q++) {
+            const f32x4 a = park[4 * sl + q][threadIdx.x], d = park[4 * sl + 2 + q][threadIdx.x];
+#pragma unroll
+            for (int j = 0; j < 4; j++) {
+                xp[4 * q + j] = a[j];
+                dp[4 * q + j] = d[j];
+            }
+        }
+    };
+    auto apply = [&](const Row<GF> &r, float lrr, const float *xp, const float *dp) {
+        float xn[8];
+#pragma unroll
+        for (int j = 0; j < 8; j++) xn[j] = xp[j] - lrr * dp[j];
+        r.store(x, xn);
+    };
+    float fx[8], fm[8], fv[8];  // the next row's state
+    RawGrad<SRC> fg;
+    auto fetch = [&](const Row<GF> &r) {
+        if (r.row >= r.t_hi) return;
+        r.load(x, fx);
+        r.load(m, fm);
+        r.load(v, fv);
+        if constexpr (!kPeers) fg.load(ga, r);
+        // a message's step waits here: with the loads left in flight over the
+        // sums and the leaving row's stores it ran 101 instead of 98 us on
+        // ALBERT-large (the fused average the other way round: 188 against 198)
+        if (!kPeers) __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt(0)
+    };
+    UnitAt t(ch, blockIdx.x, 0), to(ch, blockIdx.x, 0);
+    fetch(Row<GF>(t.row, t.t_hi));
+    double s0 = 0.0, s1 = 0.0;
+    uint32_t b = blockIdx.x;
+#pragma unroll 1
+    for (;; it++) {
+        const uint32_t half = it & 1;
+        const Row<GF> r(t.row + (uint64_t)half * kRow, t.t_hi);
+        // the row that leaves the line in this turn: its tensor's word is
+        // loaded while the new row is worked on
+        if (it >= S && (it - S) % 2 == 0) to = UnitAt(ch, blockIdx.x + (it - S) / 2 * G, to.k);
+        const Row<GF> ro(to.row + (uint64_t)((it - S) & 1) * kRow, to.t_hi);
+        const bool leaves = it >= S && to.held(op) && ro.row < to.t_hi;
+        unsigned long long q = 0;
+        if (leaves) q = __hip_atomic_load(ws.trust + ch.t0 + to.k, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        float xv[8], dv[8];
+        if (kPeers ? r.e0() < r.t_hi : r.row < r.t_hi) {
+            const float lam = (ch.flags[t.k] & 1u) ? op.wd : 0.0f;
+            float g[8], mv[8], vv[8];
+            if constexpr (kPeers) load_grad<SRC, kLinePeerBatch>(ga, pt, r.e0(), count8(r.e0(), r.t_hi), g);
+            else fg.decode(g);
+#pragma unroll
+            for (int j = 0; j < 8; j++) {
+                xv[j] = fx[j];
+                mv[j] = fmaf(op.beta1, fm[j], op.omb1 * g[j]);
+                vv[j] = fmaf(op.beta2, fv[j], op.omb2 * (g[j] * g[j]));
+                dv[j] = lamb_dir(mv[j], vv[j], xv[j], lam, op);
+                // past the end: no part of the sums, whatever eps and c2 are
+                if (!r.full() && !r.has(j)) dv[j] = 0.0f;
+                s0 += (double)xv[j] * (double)xv[j];
+                s1 += (double)dv[j] * (double)dv[j];
+            }
+            r.store(m, mv);
+            r.store(v, vv);
+        }
+        const bool more = half == 0 || b + G < n;
+        const UnitAt tn = half == 0 || b + G >= n ? t : UnitAt(ch, b + G, t.k);
+        if (more) fetch(half == 0 ? Row<GF>(r.row + kRow, r.t_hi) : Row<GF>(tn.row, tn.t_hi));
+        if (half == 1) {
+            block_sum2(s0, s1);
+            unsigned long long *part = tensor_parts(ch, ws, t.k);
+            if (t.unit != t.units - 1) {
+                if (threadIdx.x == 0) put_part(part + 4 * (uint64_t)t.unit, tag, s0, s1);
+            } else {
+                // the workgroup of the tensor's last unit publishes its ratio
+                double a0 = 0.0, a1 = 0.0;
+                const bool ok = t.units == 1 || unit_sums<true>(ws, part, t.units - 1, tag, op.trust_polls, a0, a1);
+                if (threadIdx.x == 0) {
+                    double *own = (double *)(part + 4 * (uint64_t)t.unit);
+                    own[0] = s0;
+                    own[1] = s1;
+                    unsigned long long *word = ws.trust + ch.t0 + t.k;
+                    const float rt = trust_ratio<kOptLamb>(ch.flags[t.k], op, a0 + s0, a1 + s1);
+                    const uint32_t low = ok ? __float_as_uint(rt) : kFailed;
+                    const unsigned long long seen = __hip_atomic_load(word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    const uint32_t got = decide(word, seen, tag, low);
+                    if (got == kFailed) __hip_atomic_store(ws.gave_up, tag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    else if (trust_out) trust_out[ch.t0 + t.k] = rt;
+                }
+            }
+            s0 = s1 = 0.0;
+        }
+        if (leaves) {
+            const uint32_t low = __builtin_amdgcn_readfirstlane(await_ratio(ws, op, ws.trust + ch.t0 + to.k, q, tag));
+            if (low != kFailed) {
+                float xp[8], dp[8];
+                unpark(slot, xp, dp);
+                apply(ro, op.lr * __uint_as_float(low), xp, dp);
+            }
+        }
+        if (it >= NR) {
+            const float *xo = xr[NR - 1], *d = dr[NR - 1];
+#pragma unroll
+            for (int c = 0; c < 2; c++) {
+                park[4 * slot + c][threadIdx.x] = f32x4{xo[4 * c], xo[4 * c + 1], xo[4 * c + 2], xo[4 * c + 3]};
+                park[4 * slot + 2 + c][threadIdx.x] = f32x4{d[4 * c], d[4 * c + 1], d[4 * c + 2], d[4 * c + 3]};
+            }
+            slot = slot + 1 == NL ? 0 : slot + 1;
+        }
+#pragma unroll
+        for (uint32_t i = NR - 1; i > 0; i--)
+#pragma unroll
+            for (int j = 0; j < 8; j++) {
+                xr[i][j] = xr[i - 1][j];
+                dr[i][j] = dr[i - 1][j];
+            }
+#pragma unroll
+        for (int j = 0; j < 8; j++) {
+            xr[0][j] = xv[j];
+            dr[0][j] = dv[j];
+        }
+        if (!more) break;
+        t = tn;
+        if (half == 1) b += G;
+    }
+    it++;
+    // the rows still in the line: the one taken i turns before the end (`it`
+    // turns in all) has slot i - 1
+    const uint32_t left = it < S ? it : S;
+    uint32_t r_lane = kFailed;
+    if ((threadIdx.x & 63) < left) {
+        const UnitAt u(ch, blockIdx.x + (it - 1 - (threadIdx.x & 63)) / 2 * G, t.k);
+        unsigned long long *word = ws.trust + ch.t0 + u.k;
+        if (u.held(op))
+            r_lane = await_ratio(ws, op, word, __hip_atomic_load(word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT), tag);
+    }
+    for (uint32_t i = left; i > 0; i--) {
+        const UnitAt u(ch, blockIdx.x + (it - i) / 2 * G, t.k);
+        const Row<GF> r(u.row + (uint64_t)((it - i) & 1) * kRow, u.t_hi);
+        const uint32_t low = __builtin_amdgcn_readfirstlane(__shfl(r_lane, i - 1, 64));
+        if (r.row >= r.t_hi || !u.held(op) || low == kFailed) continue;
+        float xp[8], dp[8];
+        if (i > NR) {
+            // parked in turn: the newest parked row (i = NR + 1) is just before `slot`
+            const uint32_t back = i - NR;
+            unpark(slot >= back ? slot - back : slot + NL - back, xp, dp);
+        } else {
+#pragma unroll
+            for (uint32_t c = 0; c < NR; c++)
+                if (i == c + 1)
+#pragma unroll
+                    for (int j = 0; j < 8; j++) {
+                        xp[j] = xr[c][j];
+                        dp[j] = dr[c][j];
+                    }
+        }
+        apply(r, op.lr * __uint_as_float(low), xp, dp);
+    }
+}
+
+// A row from memory: u formed again by pass A's operations.
+__device__ __forceinline__ void redo_row(const OptParams &op, float *__restrict__ x, float *__restrict__ m,
+                                         float *__restrict__ v, uint64_t row, uint64_t t_hi, float lam, float lrr) {
+    const Row<true> r(row, t_hi);
+    float xv[8], mv[8], vv[8];
+    r.load(x, xv);
+    r.load(m, mv);
+    r.load(v, vv);
+#pragma unroll
+    for (int j = 0; j < 8; j++) xv[j] = xv[j] - lrr * lamb_dir(mv[j], vv[j], xv[j], lam, op);
+    r.store(x, xv);
+}
+
+// The ratio of tensor k after pass A: as decided, else from the partials.
+__device__ __forceinline__ float known_ratio(const Chunk &ch, const OptParams &op, const LineWs &ws, uint32_t k,
+                                             uint32_t tag) {
+    const unsigned long long w = ws.trust[ch.t0 + k];
+    if ((uint32_t)(w >> 32) == tag && (uint32_t)w != kFailed) return __uint_as_float((uint32_t)w);
+    const uint32_t last = ch.begin[k + 1] - ch.begin[k] - 1;
+    const unsigned long long *part = tensor_parts(ch, ws, k);
+    const double *own = (const double *)(part + 4 * (uint64_t)last);
+    __shared__ float s_r;
+    double a0, a1;
+    unit_sums<false>(ws, part, last, tag, 0, a0, a1);
+    if (threadIdx.x == 0) s_r = trust_ratio<kOptLamb>(ch.flags[k], op, a0 + own[0], a1 + own[1]);
+    __syncthreads();
+    return s_r;  // written again only past another barrier
+}
+
+// What pass A left: the rows of units it does not hold (workgroups
+// [0, n_rest), last to first: the re-reads start with what pass A touched
+// last), and all held rows of tensors that were given up, if there are any.
+// Also r = 1 of empty tensors, and the next launch's tag.
+__global__ __launch_bounds__(kWG) void lamb_b_kernel(const Chunk ch, const RestTable rt, const OptParams op,
+                                                     float *__restrict__ x, float *__restrict__ m,
+                                                     float *__restrict__ v, LineWs ws, uint32_t nonce,
+                                                     float *__restrict__ trust_out) {
+    const uint32_t epoch = ws.epoch[1];
+    const uint32_t tag = epoch + nonce;
+    if (blockIdx.x < rt.n_rest) {
+        const uint32_t q = rt.n_rest - 1 - blockIdx.x;
+        uint32_t lo = 0, hi = ch.nt;
+        while (hi - lo > 1) {
+            const uint32_t mid = (lo + hi) >> 1;
+            if (rt.begin[mid] <= q) lo = mid;
+            else hi = mid;
+        }
+        const uint64_t row = ch.base + ch.start[lo] + (uint64_t)(q - rt.begin[lo]) * kRow;
+        const float lam = (ch.flags[lo] & 1u) ? op.wd : 0.0f;
+        const float lrr = op.lr * known_ratio(ch, op, ws, lo, tag);
+        redo_row(op, x, m, v, row, ch.base + ch.start[lo + 1], lam, lrr);
+        return;
+    }
+    const uint32_t q = blockIdx.x - rt.n_rest, step = gridDim.x - rt.n_rest;
+    if (q == 0) {
+        for (uint32_t k = threadIdx.x; k < ch.nt; k += kWG)
+            if (trust_out && ch.begin[k] == ch.begin[k + 1]) trust_out[ch.t0 + k] = 1.0f;
+        if (threadIdx.x == 0) ws.epoch[0] = epoch + 1u;
+    }
+    if (*ws.gave_up != tag) return;
+    for (uint32_t k = 0; k < ch.nt; k++) {
+        const uint32_t units = ch.begin[k + 1] - ch.begin[k];
+        if (units == 0 || ws.trust[ch.t0 + k] != (((unsigned long long)tag << 32) | kFailed)) continue;
+        const uint64_t t_hi = ch.base + ch.start[k + 1];
+        const float lam = (ch.flags[k] & 1u) ? op.wd : 0.0f;
+        const float r_t = known_ratio(ch, op, ws, k, tag);
+        if (q == 0 && threadIdx.x == 0 && trust_out) trust_out[ch.t0 + k] = r_t;
+        const uint32_t first = units > op.hold ? 2 * (units - op.hold) : 0;  // the held rows: [first, 2 * units)
+        for (uint32_t i = first + q; i < 2 * units; i += step) {
+            const uint64_t row = ch.base + ch.start[k] + (uint64_t)i * kRow;
+            if (row < t_hi) redo_row(op, x, m, v, row, t_hi, lam, op.lr * r_t);
+        }
     }
 }
 
@@ -815,7 +1308,7 @@ __global__ __launch_bounds__(kWG) void accumulate_kernel(float *__restrict__ acc
     if (e0 >= n) return;
     const int cnt = (int)(n - e0 < (uint64_t)kVec ? n - e0 : (uint64_t)kVec);
     float a[8], g[8];
-    load8(acc, e0, cnt, a);
+    load8<false>(acc, e0, cnt, a);
     if (G16) {
         if (cnt == kVec) {
             unpack_fp16x8(ld_stream((const u32x4 *)((const uint16_t *)grad + e0)), g);
@@ -834,7 +1327,7 @@ __global__ __launch_bounds__(kWG) void accumulate_kernel(float *__restrict__ acc
     }
 #pragma unroll
     for (int j = 0; j < 8; j++) a[j] = fmaf(b, g[j], a[j]);
-    store8(acc, e0, cnt, a);
+    store8<false>(acc, e0, cnt, a);
 }
 
 // mean = acc / count, encoded fp16; acc zeroed when reset.
@@ -844,7 +1337,7 @@ __global__ __launch_bounds__(kWG) void finalize_fp16_kernel(float *__restrict__ 
     if (e0 >= n) return;
     const int cnt = (int)(n - e0 < (uint64_t)kVec ? n - e0 : (uint64_t)kVec);
     float a[8];
-    load8(acc, e0, cnt, a);
+    load8<false>(acc, e0, cnt, a);
 #pragma unroll
     for (int j = 0; j < 8; j++) a[j] = a[j] / count;
     if (cnt == kVec) {
@@ -854,7 +1347,7 @@ __global__ __launch_bounds__(kWG) void finalize_fp16_kernel(float *__restrict__ 
     }
     if (reset) {
         const float z[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-        store8(acc, e0, cnt, z);
+        store8<false>(acc, e0, cnt, z);
     }
 }
 
@@ -875,7 +1368,7 @@ __global__ __launch_bounds__(kWG) void finalize_i8_kernel(float *__restrict__ ac
         const uint64_t b0 = i8_lane_base(blk);
         if ((blk + 1) * kI8Block <= n) {
 #pragma unroll
-            for (int q = 0; q < 4; q++) st_stream((f32x4 *)(acc + I8_ELEM(b0, q, 0)), f32x4{0.0f, 0.0f, 0.0f, 0.0f});
+            for (int q = 0; q < 4; q++) *(f32x4 *)(acc + I8_ELEM(b0, q, 0)) = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
         } else {
 #pragma unroll
             for (int q = 0; q < 4; q++)
@@ -958,45 +1451,74 @@ hipError_t launch_reduce_i8(const GroupTable &gt, uint64_t len, const ChainArgs 
     DEDLOC_LAUNCH(grid, reduce_i8_kernel<DEDLOC_I8_BATCH>, s, gt, len, ca);
 }
 
-template <int OPT>
-static hipError_t launch_a(int src, const Chunk &ch, uint32_t n_tiles, const PeerTable &p, const GradArgs &ga,
-                           const OptParams &op, float *x, float *m, float *v, const LambWs &ws, hipStream_t s) {
+hipError_t launch_lamb_a(int src, const Chunk &ch, uint32_t n_groups, const PeerTable &pt, const GradArgs &ga,
+                         const OptParams &op, float *x, float *m, float *v, const LineWs &ws, uint32_t nonce,
+                         float *trust_out, hipStream_t s) {
+    const dim3 g(n_groups);
     switch (src) {
-    case kSrcF32: DEDLOC_LAUNCH(dim3(n_tiles), (opt_a_kernel<kSrcF32, OPT>), s, ch, p, ga, op, x, m, v, ws);
-    case kSrcFP16: DEDLOC_LAUNCH(dim3(n_tiles), (opt_a_kernel<kSrcFP16, OPT>), s, ch, p, ga, op, x, m, v, ws);
-    case kSrcI8: DEDLOC_LAUNCH(dim3(n_tiles), (opt_a_kernel<kSrcI8, OPT>), s, ch, p, ga, op, x, m, v, ws);
-    case kSrcPeersFP16: DEDLOC_LAUNCH(dim3(n_tiles), (opt_a_kernel<kSrcPeersFP16, OPT>), s, ch, p, ga, op, x, m, v, ws);
-    case kSrcPeersFP16Chain:
-        DEDLOC_LAUNCH(dim3(n_tiles), (opt_a_kernel<kSrcPeersFP16Chain, OPT>), s, ch, p, ga, op, x, m, v, ws);
-    case kSrcPeersFP16Local:
-        DEDLOC_LAUNCH(dim3(n_tiles), (opt_a_kernel<kSrcPeersFP16Local, OPT>), s, ch, p, ga, op, x, m, v, ws);
+#define DEDLOC_CASE(SRC) \
+    case SRC: DEDLOC_LAUNCH(g, lamb_a_kernel<SRC>, s, ch, pt, ga, op, x, m, v, ws, nonce, trust_out)
+    DEDLOC_CASE(kSrcF32);
+    DEDLOC_CASE(kSrcFP16);
+    DEDLOC_CASE(kSrcI8);
+    DEDLOC_CASE(kSrcPeersFP16);
+    DEDLOC_CASE(kSrcPeersFP16Chain);
+    DEDLOC_CASE(kSrcPeersFP16Local);
+#undef DEDLOC_CASE
     default: return hipErrorInvalidValue;
     }
 }
 
-hipError_t launch_opt_a(int opt, int src, const Chunk &ch, uint32_t n_tiles, const PeerTable *pt,
-                        const GradArgs &ga, const OptParams &op, float *x, float *m, float *v,
-                        const LambWs &ws, hipStream_t s) {
-    static const PeerTable empty = {};
-    const PeerTable &p = pt ? *pt : empty;
-    if (opt == kOptLamb) return launch_a<kOptLamb>(src, ch, n_tiles, p, ga, op, x, m, v, ws, s);
-    if (opt == kOptLars) return launch_a<kOptLars>(src, ch, n_tiles, p, ga, op, x, m, v, ws, s);
-    return hipErrorInvalidValue;
+hipError_t launch_lamb_b(const Chunk &ch, const RestTable &rt, uint32_t n_check, const OptParams &op, float *x, float *m,
+                         float *v, const LineWs &ws, uint32_t nonce, float *trust_out, hipStream_t s) {
+    DEDLOC_LAUNCH(dim3(rt.n_rest + n_check), lamb_b_kernel, s, ch, rt, op, x, m, v, ws, nonce, trust_out);
 }
 
-hipError_t launch_opt_b(int opt, int src, const Chunk &ch, uint32_t n_tiles, const GradArgs &ga,
-                        const OptParams &op, float *x, float *m, float *v, const LambWs &ws, uint32_t nonce,
-                        float *trust_out, hipStream_t s) {
-    const dim3 g(ch.nt + n_tiles);  // one producer per tensor, then every tile
+template <int OPT, bool NT>
+static hipError_t launch_a(int src, const Chunk &ch, const PeerTable &p, const GradArgs &ga, const OptParams &op,
+                           float *x, float *m, float *v, const TileWs &ws, hipStream_t s) {
+    const dim3 g(ch.begin[ch.nt]);
+    switch (src) {
+#define DEDLOC_CASE(SRC) \
+    case SRC: DEDLOC_LAUNCH(g, (opt_a_kernel<SRC, OPT, NT>), s, ch, p, ga, op, x, m, v, ws)
+    DEDLOC_CASE(kSrcF32);
+    DEDLOC_CASE(kSrcFP16);
+    DEDLOC_CASE(kSrcI8);
+    DEDLOC_CASE(kSrcPeersFP16);
+    DEDLOC_CASE(kSrcPeersFP16Chain);
+    DEDLOC_CASE(kSrcPeersFP16Local);
+#undef DEDLOC_CASE
+    default: return hipErrorInvalidValue;
+    }
+}
+
+hipError_t launch_opt_a(int opt, int src, bool nt, const Chunk &ch, const PeerTable &p, const GradArgs &ga,
+                        const OptParams &op, float *x, float *m, float *v, const TileWs &ws, hipStream_t s) {
     if (opt == kOptLamb)
-        DEDLOC_LAUNCH(g, (opt_b_kernel<kSrcF32, kOptLamb>), s, ch, ga, op, x, m, v, ws, nonce, trust_out);
-    if (opt != kOptLars) return hipErrorInvalidValue;
+        return nt ? launch_a<kOptLamb, true>(src, ch, p, ga, op, x, m, v, ws, s)
+                  : launch_a<kOptLamb, false>(src, ch, p, ga, op, x, m, v, ws, s);
+    // LARS's pass A reads and keeps only x: no non-temporal form of its own
+    return launch_a<kOptLars, false>(src, ch, p, ga, op, x, m, v, ws, s);
+}
+
+template <bool NT>
+static hipError_t launch_b(int opt, int src, const Chunk &ch, const GradArgs &ga, const OptParams &op, float *x,
+                           float *m, float *v, const TileWs &ws, uint32_t nonce, float *trust_out, hipStream_t s) {
+    const dim3 g(ch.nt + ch.begin[ch.nt]);  // one producer per tensor, then every tile
+    if (opt == kOptLamb)
+        DEDLOC_LAUNCH(g, (opt_b_kernel<kSrcF32, kOptLamb, NT>), s, ch, ga, op, x, m, v, ws, nonce, trust_out);
     switch (src) {
-    case kSrcF32: DEDLOC_LAUNCH(g, (opt_b_kernel<kSrcF32, kOptLars>), s, ch, ga, op, x, m, v, ws, nonce, trust_out);
-    case kSrcFP16: DEDLOC_LAUNCH(g, (opt_b_kernel<kSrcFP16, kOptLars>), s, ch, ga, op, x, m, v, ws, nonce, trust_out);
-    case kSrcI8: DEDLOC_LAUNCH(g, (opt_b_kernel<kSrcI8, kOptLars>), s, ch, ga, op, x, m, v, ws, nonce, trust_out);
+    case kSrcF32: DEDLOC_LAUNCH(g, (opt_b_kernel<kSrcF32, kOptLars, NT>), s, ch, ga, op, x, m, v, ws, nonce, trust_out);
+    case kSrcFP16: DEDLOC_LAUNCH(g, (opt_b_kernel<kSrcFP16, kOptLars, NT>), s, ch, ga, op, x, m, v, ws, nonce, trust_out);
+    case kSrcI8: DEDLOC_LAUNCH(g, (opt_b_kernel<kSrcI8, kOptLars, NT>), s, ch, ga, op, x, m, v, ws, nonce, trust_out);
     default: return hipErrorInvalidValue;
     }
+}
+
+hipError_t launch_opt_b(int opt, int src, bool nt, const Chunk &ch, const GradArgs &ga, const OptParams &op, float *x,
+                        float *m, float *v, const TileWs &ws, uint32_t nonce, float *trust_out, hipStream_t s) {
+    return nt ? launch_b<true>(opt, src, ch, ga, op, x, m, v, ws, nonce, trust_out, s)
+              : launch_b<false>(opt, src, ch, ga, op, x, m, v, ws, nonce, trust_out, s);
 }
 
 hipError_t launch_accumulate(float *acc, const void *grad, bool fp16, uint64_t n, float b, hipStream_t s) {

@@ -1,0 +1,142 @@
+"""LAMB in one pass (GPU): tables large enough that x and u are held on chip
+until each tensor's trust ratio is known.
+
+Sizes where the pass can go wrong: tensors ending at, just before and just
+past a row (2048 elements) and a unit (two rows), tensors of one element's
+vector, a ragged last tensor, a tensor with more units than the grid holds,
+and the smallest table that takes the pass.  Every gradient source against the
+oracle; every poll bound, and two steps at once on two streams (whose grids
+may keep each other's workgroups waiting), give the same bits."""
+
+import numpy as np
+import pytest
+
+import oracle
+from paper_2106_10207_amd import dedloc as D
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+DEV = "cuda"
+SMALLEST = 1 << 23
+# edges of rows and units, then tensors that bring the table to one-pass size
+EDGES = [2048, 2040, 2056, 4096, 4088, 4104, 8, 6144, 0, 1 << 20]
+TABLES = {
+    "smallest": [SMALLEST],
+    "edges": EDGES + [SMALLEST - sum(EDGES) + 8],
+    "ragged": [5 * 4096 + 2048, SMALLEST, 4096 * 3 + 1],
+    "beyond_the_line": [1 << 20, 2 * 768 * 4096 + 3 * 4096 + 16, 1 << 20, 2051],
+}
+
+
+def _inputs(sizes, src, seed=3):
+    off = np.concatenate([[0], np.cumsum(sizes)]).astype(np.uint64)
+    P = int(off[-1])
+    gen = torch.Generator(device=DEV)
+    gen.manual_seed(seed)
+    x = torch.randn(P, generator=gen, device=DEV).mul_(0.02)
+    m = torch.randn(P, generator=gen, device=DEV).mul_(1e-4)
+    v = torch.randn(P, generator=gen, device=DEV).mul_(1e-3).square_()
+    g = torch.randn(P, generator=gen, device=DEV).mul_(1e-3)
+    scales = None
+    grad = g
+    if src != "f32":
+        grad, scales = D.dedloc_encode(g, D.CODECS[src])
+        g = D.dedloc_decode(grad, scales, P, D.CODECS[src])
+    flags = np.array([(3, 2, 1, 3)[i % 4] for i in range(len(sizes))], np.uint8)
+    return off, flags, x, m, v, g, grad, scales
+
+
+CFG = dict(lr=1e-2, beta1=0.9, beta2=0.999, eps=1e-6, weight_decay=0.01, step=3)
+
+
+def _step(t, src, off, flags, grad, scales, ws=None, stream=None):
+    x, m, v = (a.clone() for a in t)
+    tr = torch.full((len(flags),), -1.0, device=DEV)
+    ws = D.make_workspace(x.numel(), off) if ws is None else ws
+    torch.cuda.synchronize()
+    D.dedloc_lamb_step(x, m, v, grad, off, flags, D.lamb_cfg(**CFG), D.CODECS[src], scales, trust_out=tr, ws=ws,
+                       stream=stream)
+    return x, m, v, tr
+
+
+def _check(got, want, xmax):
+    x, m, v, tr = (t.cpu().numpy() for t in got)
+    xo, mo, vo, to = want
+    assert np.array_equal(m.view(np.uint32), mo.view(np.uint32))
+    assert np.array_equal(v.view(np.uint32), vo.view(np.uint32))
+    assert np.allclose(tr, to, rtol=1e-6, atol=0)
+    assert float(np.max(np.abs(x.astype(np.float64) - xo))) <= 1e-5 * xmax
+
+
+@pytest.mark.parametrize("table", list(TABLES))
+@pytest.mark.parametrize("src", ["f32", "fp16", "i8"])
+def test_one_pass_step(table, src):
+    print(f"\n[one pass] {table} {src}", flush=True)
+    off, flags, x, m, v, g, grad, scales = _inputs(TABLES[table], src)
+    host = [t.cpu().numpy() for t in (x, m, v, g)]
+    want = oracle.lamb(*host, off, flags, oracle.lamb_cfg(**CFG))
+    got = _step((x, m, v), src, off, flags, grad, scales)
+    _check(got, want, float(np.max(np.abs(host[0]))))
+    old = D.dedloc_test_trust_polls(4096)
+    try:
+        for polls in (0, 1):  # every tensor, or some, given up to the second pass
+            D.dedloc_test_trust_polls(polls)
+            for a, b in zip(got, _step((x, m, v), src, off, flags, grad, scales)):
+                assert torch.equal(a.view(torch.int32), b.view(torch.int32)), polls
+    finally:
+        D.dedloc_test_trust_polls(old)
+
+
+@pytest.mark.parametrize("table", ["edges", "ragged"])
+@pytest.mark.parametrize("n_peers,local", [(3, None), (9, 4), (66, None), (66, 65)])
+def test_one_pass_round(table, n_peers, local):
+    """The fused average inside the pass (66 peers: its chained form), bit for
+    bit against the average and the step called one after the other."""
+    print(f"\n[one pass] round {table} {n_peers} {local}", flush=True)
+    off, flags, x, m, v, g, _, _ = _inputs(TABLES[table], "f32")
+    P = x.numel()
+    counts = np.arange(1, n_peers + 1, dtype=np.uint32)
+    codes = [D.dedloc_encode(torch.roll(g, 8 * p), D.DEDLOC_CODEC_FP16)[0] for p in range(n_peers)]
+    want_codes = torch.empty(P, dtype=torch.int16, device=DEV)
+    mean = torch.empty(P, device=DEV)
+    D.dedloc_reduce_shard(codes, counts, P, D.DEDLOC_CODEC_FP16, out_codes=want_codes, out_mean=mean)
+    want = _step((x, m, v), "fp16", off, flags, want_codes, None)
+    own = None
+    if local is not None:
+        own = codes[local].clone()
+        codes[local].fill_(0x7E00)  # written by the round
+    xr, mr, vr = x.clone(), m.clone(), v.clone()
+    tr = torch.full((len(flags),), -1.0, device=DEV)
+    got_mean = torch.empty(P, device=DEV)
+    out, _ = D.dedloc_round(codes, counts, D.dedloc_partition(P, n_peers), D.DEDLOC_CODEC_FP16, xr, mr, vr, off, flags,
+                            D.lamb_cfg(**CFG), trust_out=tr, out_mean=got_mean,
+                            local=None if local is None else (local, torch.roll(g, 8 * local).contiguous()))
+    torch.cuda.synchronize()
+    assert torch.equal(out, want_codes) and torch.equal(got_mean, mean)
+    if own is not None:
+        assert torch.equal(codes[local], own)
+    # the two add a row's squares in different lane orders: the ratio is the
+    # same to fp32 rounding, everything before it bit for bit
+    assert torch.equal(mr, want[1]) and torch.equal(vr, want[2])
+    assert torch.allclose(tr, want[3], rtol=1e-6, atol=0)
+    assert float((xr - want[0]).abs().max()) <= 1e-5 * float(x.abs().max())
+
+
+def test_two_steps_at_once():
+    """Two one-pass steps on two streams, each with its own workspace: their
+    persistent grids share the CUs, so tensors of either may be given up."""
+    print("\n[one pass] two streams", flush=True)
+    off, flags, x, m, v, g, _, _ = _inputs([1 << 21] * 5, "f32")
+    want = _step((x, m, v), "f32", off, flags, g, None)
+    torch.cuda.synchronize()
+    streams = [torch.cuda.Stream() for _ in range(2)]
+    sets = [[t.clone() for t in (x, m, v)] + [torch.full((len(flags),), -1.0, device=DEV), D.make_workspace(x.numel(), off)]
+            for _ in streams]
+    torch.cuda.synchronize()
+    for s, (a, b, c, tr, ws) in zip(streams, sets):
+        D.dedloc_lamb_step(a, b, c, g, off, flags, D.lamb_cfg(**CFG), trust_out=tr, ws=ws, stream=s)
+    torch.cuda.synchronize()
+    for got in sets:
+        for a, b in zip(got[:4], want):
+            assert torch.equal(a.view(torch.int32), b.view(torch.int32))
