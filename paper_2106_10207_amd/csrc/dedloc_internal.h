@@ -87,6 +87,10 @@ struct ChainArgs {
     float *acc_out;       // the sum after this launch (the mean after the last launch; nullable)
     int final_pass;       // encode into the group outputs
     LocalArgs local;
+    // the encoded average is written `copies` times, at these strides from the
+    // group's output (one group; a plain reduce writes it once)
+    uint32_t copies;
+    uint64_t code_stride, scale_stride;  // bytes, floats
 };
 
 // A run of consecutive tensors handled by one optimizer launch (it spans

@@ -340,7 +340,7 @@ __global__ __launch_bounds__(kWG) void reduce_fp16_kernel(const GroupTable gt, u
     const uint32_t g = blockIdx.y;
     const uint32_t p_lo = gt.gbegin[g], p_hi = gt.gbegin[g + 1];
     if (p_lo == p_hi) return;  // a group without samples produces nothing
-    uint16_t *__restrict__ out = (uint16_t *)gt.out[g];
+    uint16_t *out = (uint16_t *)gt.out[g];
     float *mean = ca.acc_out;  // may alias ca.acc_in (same element, same lane)
     const uint64_t e0 = ((uint64_t)blockIdx.x * kWG + threadIdx.x) * kVec;
     const bool local = B == kPeerBatch && ca.local.pos >= 0;  // single group: p_lo = 0
@@ -349,7 +349,10 @@ __global__ __launch_bounds__(kWG) void reduce_fp16_kernel(const GroupTable gt, u
         init8(ca.acc_in, e0, acc);
         if (local) reduce_fp16x8_local<B>(gt.pt, p_hi, ca.local.pos, ca.local, e0, acc);
         else reduce_fp16x8<B>(gt.pt, p_lo, p_hi, e0, acc);
-        if (ca.final_pass) *(u32x4 *)(out + e0) = pack_fp16x8(acc);
+        if (ca.final_pass) {
+            const u32x4 c = pack_fp16x8(acc);
+            for (uint32_t k = 0; k < ca.copies; k++) *(u32x4 *)((char *)(out + e0) + k * ca.code_stride) = c;
+        }
         if (mean) {
             *(f32x4 *)(mean + e0) = f32x4{acc[0], acc[1], acc[2], acc[3]};
             *(f32x4 *)(mean + e0 + 4) = f32x4{acc[4], acc[5], acc[6], acc[7]};
@@ -359,7 +362,8 @@ __global__ __launch_bounds__(kWG) void reduce_fp16_kernel(const GroupTable gt, u
             const float a0 = ca.acc_in ? ca.acc_in[e] : 0.0f;
             const float a = local ? reduce_fp16_one_local(gt.pt, p_hi, ca.local.pos, ca.local, e, a0)
                                   : reduce_fp16_one(gt.pt, p_lo, p_hi, e, a0);
-            if (ca.final_pass) out[e] = (uint16_t)f2h(a);
+            if (ca.final_pass)
+                for (uint32_t k = 0; k < ca.copies; k++) *(uint16_t *)((char *)(out + e) + k * ca.code_stride) = (uint16_t)f2h(a);
             if (mean) mean[e] = a;
         }
     }
@@ -423,8 +427,8 @@ __global__ __launch_bounds__(kWG) void reduce_i8_kernel(const GroupTable gt, uin
     const uint32_t g = blockIdx.y;
     const uint32_t p_lo = gt.gbegin[g], p_hi = gt.gbegin[g + 1];
     if (p_lo == p_hi) return;  // a group without samples produces nothing
-    int8_t *__restrict__ out = (int8_t *)gt.out[g];
-    float *__restrict__ out_scales = gt.out_scales[g];
+    int8_t *out = (int8_t *)gt.out[g];
+    float *out_scales = gt.out_scales[g];
     const PeerTable &pt = gt.pt;
     const uint64_t blk = (uint64_t)blockIdx.x * (kWG / 64) +
                          (uint64_t)__builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -457,13 +461,15 @@ __global__ __launch_bounds__(kWG) void reduce_i8_kernel(const GroupTable gt, uin
     if (!ca.final_pass) return;  // wave-uniform
     float s;
     const u32x4 c = encode_i8_wave(acc, s);  // out-of-range lanes hold 0
-    if (full) {
-        *(u32x4 *)(out + e0) = c;
-    } else {
-        for (int k = 0; k < kI8PerLane; k++)
-            if (e0 + k < len) out[e0 + k] = (int8_t)(c[k >> 2] >> (8 * (k & 3)));
+    for (uint32_t n = 0; n < ca.copies; n++, out += ca.code_stride, out_scales += ca.scale_stride) {
+        if (full) {
+            *(u32x4 *)(out + e0) = c;
+        } else {
+            for (int k = 0; k < kI8PerLane; k++)
+                if (e0 + k < len) out[e0 + k] = (int8_t)(c[k >> 2] >> (8 * (k & 3)));
+        }
+        if ((threadIdx.x & 63) == 0) out_scales[blk] = s;
     }
-    if ((threadIdx.x & 63) == 0) out_scales[blk] = s;
 }
 
 // ------------------------------------------------------- LAMB and LARS
