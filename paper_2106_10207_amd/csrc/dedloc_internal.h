@@ -21,7 +21,7 @@ namespace dedloc {
 #define DEDLOC_TRUST_UNROLL 8   // tile partials loaded per lane before summing
 #endif
 #ifndef DEDLOC_I8_BATCH
-#define DEDLOC_I8_BATCH 16    // int8 peer messages loaded per batch in the reduce
+#define DEDLOC_I8_BATCH 4     // int8 peer messages loaded per batch in the reduce
 #endif
 
 constexpr int kWG = 256;               // threads per workgroup: 4 wave64
@@ -44,6 +44,8 @@ constexpr int kLinePeerBatch = 4;
 constexpr int kMaxPeers = 64;          // peer table lives in the kernel arguments
 constexpr int kI8Block = 1024;         // int8 codec block = one wave64 x 16 codes
 constexpr int kI8PerLane = 16;
+// 60 peers' 8M elements: 4 83.5 us, 8 99.6, 12 90.1, 16 88.9; 4 also leaves room for 8 waves a SIMD
+constexpr int kI8Batch = DEDLOC_I8_BATCH;
 constexpr int kChunkTensors = 192;     // tensors described per LAMB launch
 
 // Active peers (counts > 0) in ascending peer order, with their weights.

@@ -90,6 +90,17 @@ __device__ __forceinline__ void block_sum2(double &a, double &b) {
     __syncthreads();
 }
 
+// Lane layout of rows of 2048 fp32 elements, of which a wave works on 512:
+// lane l holds elements 4l..4l+3 and 256+4l..256+4l+3 of its wave's 512, so
+// that every 16-byte access of the wave covers 1 KB without gaps.  With eight
+// consecutive elements per lane (two accesses at a 32-byte stride) a stream of
+// 16 bytes read and 12 written per element ran at 5.2 TB/s, with or without
+// non-temporal hints; without gaps and with both hints it runs at 5.7 to 6.0
+// TB/s (17.7M and 268M elements).
+__device__ __forceinline__ uint32_t row_at(int h) {
+    return (threadIdx.x & ~63u) * kVec + 256 * h + 4 * (threadIdx.x & 63);
+}
+
 // Encode one int8 block held by a wave: 16 values per lane (lanes or values
 // past the end hold zero).  Returns the codes packed in a u32x4 and the
 // block scale (same on every lane).
@@ -141,26 +152,34 @@ __device__ __forceinline__ u32x4 encode_i8_wave(const float *val, float &scale) 
 
 __global__ __launch_bounds__(kWG) void encode_fp16_kernel(const float *__restrict__ x, uint64_t n,
                                                           uint16_t *__restrict__ codes) {
-    const uint64_t e0 = ((uint64_t)blockIdx.x * kWG + threadIdx.x) * kVec;
-    if (e0 + kVec <= n) {
-        const f32x4 a = ld_stream((const f32x4 *)(x + e0)), b = ld_stream((const f32x4 *)(x + e0 + 4));
-        float v[8] = {a[0], a[1], a[2], a[3], b[0], b[1], b[2], b[3]};
-        st_msg((u32x4 *)(codes + e0), pack_fp16x8(v));
+    const uint64_t row = (uint64_t)blockIdx.x * kRow;
+    if (row + kRow <= n) {
+#pragma unroll
+        for (int h = 0; h < 2; h++) {
+            const f32x4 a = ld_stream((const f32x4 *)(x + row + row_at(h)));
+            // plain stores: the message is read next (decoded at once, 17.7M
+            // elements 37.1 -> 33.3 us, 60M 116.8 -> 106.4)
+            *(u32x2 *)(codes + row + row_at(h)) = u32x2{f2h(a[0]) | (f2h(a[1]) << 16), f2h(a[2]) | (f2h(a[3]) << 16)};
+        }
     } else {
-        for (uint64_t e = e0; e < n; e++) codes[e] = (uint16_t)f2h(x[e]);
+        for (uint64_t e = row + threadIdx.x; e < n; e += kWG) codes[e] = (uint16_t)f2h(x[e]);
     }
 }
 
+// Non-temporal stores: the output is twice the message, and both it and the
+// decoded int8 vector ran 4 to 8% faster with them (17.7M to 60M elements).
 __global__ __launch_bounds__(kWG) void decode_fp16_kernel(const uint16_t *__restrict__ codes, uint64_t n,
                                                           float *__restrict__ out) {
-    const uint64_t e0 = ((uint64_t)blockIdx.x * kWG + threadIdx.x) * kVec;
-    if (e0 + kVec <= n) {
-        float v[8];
-        unpack_fp16x8(*(const u32x4 *)(codes + e0), v);
-        *(f32x4 *)(out + e0) = f32x4{v[0], v[1], v[2], v[3]};
-        *(f32x4 *)(out + e0 + 4) = f32x4{v[4], v[5], v[6], v[7]};
+    const uint64_t row = (uint64_t)blockIdx.x * kRow;
+    if (row + kRow <= n) {
+#pragma unroll
+        for (int h = 0; h < 2; h++) {
+            const u32x2 c = *(const u32x2 *)(codes + row + row_at(h));
+            __builtin_nontemporal_store(f32x4{h2f(c[0] & 0xffffu), h2f(c[0] >> 16), h2f(c[1] & 0xffffu), h2f(c[1] >> 16)},
+                                        (f32x4 *)(out + row + row_at(h)));
+        }
     } else {
-        for (uint64_t e = e0; e < n; e++) out[e] = h2f(codes[e]);
+        for (uint64_t e = row + threadIdx.x; e < n; e += kWG) out[e] = h2f(codes[e]);
     }
 }
 
@@ -238,8 +257,8 @@ __global__ __launch_bounds__(kWG) void decode_i8_kernel(const int8_t *__restrict
 #pragma unroll
         for (int q = 0; q < 4; q++) {
             const unsigned c = *(const unsigned *)(codes + I8_ELEM(b0, q, 0));
-            *(f32x4 *)(out + I8_ELEM(b0, q, 0)) = f32x4{sbyte(c, 0) * s, sbyte(c, 1) * s, sbyte(c, 2) * s,
-                                                        sbyte(c, 3) * s};
+            __builtin_nontemporal_store(f32x4{sbyte(c, 0) * s, sbyte(c, 1) * s, sbyte(c, 2) * s, sbyte(c, 3) * s},
+                                        (f32x4 *)(out + I8_ELEM(b0, q, 0)));
         }
     } else {
 #pragma unroll
@@ -820,17 +839,7 @@ __global__ __launch_bounds__(kWG) void opt_b_kernel(const Chunk ch, const GradAr
 
 // ------------------------------------------------------ LAMB in one pass
 
-// Lane layout of LAMB's rows of 2048 elements, of which a wave works on 512.
-// GF: lane l holds elements 4l..4l+3 and 256+4l..256+4l+3 of its wave's 512,
-// so that every 16-byte access of the wave covers 1 KB without gaps.  With eight consecutive elements per lane (two accesses at a
-// 32-byte stride) a stream of 16 bytes read and 12 written per element ran at
-// 5.2 TB/s, with or without non-temporal hints; without gaps and with both
-// hints it runs at 5.7 to 6.0 TB/s (17.7M and 268M elements).
-__device__ __forceinline__ uint32_t row_at(int h) {
-    return (threadIdx.x & ~63u) * kVec + 256 * h + 4 * (threadIdx.x & 63);
-}
-
-// The fused average keeps eight consecutive elements per lane, which its
+// LAMB's rows without gaps in a wave's accesses (GF: row_at's layout).  The fused average keeps eight consecutive elements per lane, which its
 // 16-byte message accesses need.
 template <bool GF>
 struct Row {
@@ -1307,53 +1316,54 @@ __global__ __launch_bounds__(kWG) void lamb_b_kernel(const Chunk ch, const RestT
 
 // ------------------------------------------------ local accumulation
 // acc = fma(b, g, acc): a micro-batch of b samples with mean gradient g.
+// acc is read again by the next micro-batch (plain accesses: the Infinity
+// Cache keeps a vector of ordinary size), the gradient is not.
 template <bool G16>
 __global__ __launch_bounds__(kWG) void accumulate_kernel(float *__restrict__ acc, const void *__restrict__ grad,
                                                          uint64_t n, float b) {
-    const uint64_t e0 = ((uint64_t)blockIdx.x * kWG + threadIdx.x) * kVec;
-    if (e0 >= n) return;
-    const int cnt = (int)(n - e0 < (uint64_t)kVec ? n - e0 : (uint64_t)kVec);
-    float a[8], g[8];
-    load8<false>(acc, e0, cnt, a);
-    if (G16) {
-        if (cnt == kVec) {
-            unpack_fp16x8(ld_stream((const u32x4 *)((const uint16_t *)grad + e0)), g);
-        } else {
-            for (int j = 0; j < kVec; j++) g[j] = j < cnt ? h2f(((const uint16_t *)grad)[e0 + j]) : 0.0f;
+    const uint64_t row = (uint64_t)blockIdx.x * kRow;
+    if (row + kRow <= n) {
+        f32x4 a[2], g[2];
+#pragma unroll
+        for (int h = 0; h < 2; h++) {
+            a[h] = *(const f32x4 *)(acc + row + row_at(h));
+            if (G16) {
+                const u32x2 c = ld_stream((const u32x2 *)((const uint16_t *)grad + row + row_at(h)));
+                g[h] = f32x4{h2f(c[0] & 0xffffu), h2f(c[0] >> 16), h2f(c[1] & 0xffffu), h2f(c[1] >> 16)};
+            } else {
+                g[h] = ld_stream((const f32x4 *)((const float *)grad + row + row_at(h)));
+            }
+        }
+#pragma unroll
+        for (int h = 0; h < 2; h++) {
+#pragma unroll
+            for (int j = 0; j < 4; j++) a[h][j] = fmaf(b, g[h][j], a[h][j]);
+            *(f32x4 *)(acc + row + row_at(h)) = a[h];
         }
     } else {
-        if (cnt == kVec) {
-            const f32x4 p = ld_stream((const f32x4 *)((const float *)grad + e0));
-            const f32x4 q = ld_stream((const f32x4 *)((const float *)grad + e0 + 4));
-            g[0] = p[0]; g[1] = p[1]; g[2] = p[2]; g[3] = p[3];
-            g[4] = q[0]; g[5] = q[1]; g[6] = q[2]; g[7] = q[3];
-        } else {
-            for (int j = 0; j < kVec; j++) g[j] = j < cnt ? ((const float *)grad)[e0 + j] : 0.0f;
-        }
+        for (uint64_t e = row + threadIdx.x; e < n; e += kWG)
+            acc[e] = fmaf(b, G16 ? h2f(((const uint16_t *)grad)[e]) : ((const float *)grad)[e], acc[e]);
     }
-#pragma unroll
-    for (int j = 0; j < 8; j++) a[j] = fmaf(b, g[j], a[j]);
-    store8<false>(acc, e0, cnt, a);
 }
 
 // mean = acc / count, encoded fp16; acc zeroed when reset.
 __global__ __launch_bounds__(kWG) void finalize_fp16_kernel(float *__restrict__ acc, uint64_t n, float count,
                                                             uint16_t *__restrict__ codes, int reset) {
-    const uint64_t e0 = ((uint64_t)blockIdx.x * kWG + threadIdx.x) * kVec;
-    if (e0 >= n) return;
-    const int cnt = (int)(n - e0 < (uint64_t)kVec ? n - e0 : (uint64_t)kVec);
-    float a[8];
-    load8<false>(acc, e0, cnt, a);
+    const uint64_t row = (uint64_t)blockIdx.x * kRow;
+    if (row + kRow <= n) {
 #pragma unroll
-    for (int j = 0; j < 8; j++) a[j] = a[j] / count;
-    if (cnt == kVec) {
-        st_msg((u32x4 *)(codes + e0), pack_fp16x8(a));
+        for (int h = 0; h < 2; h++) {
+            f32x4 *p = (f32x4 *)(acc + row + row_at(h));
+            const f32x4 a = *p;
+            st_msg((u32x2 *)(codes + row + row_at(h)), u32x2{f2h(a[0] / count) | (f2h(a[1] / count) << 16),
+                                                             f2h(a[2] / count) | (f2h(a[3] / count) << 16)});
+            if (reset) *p = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+        }
     } else {
-        for (int j = 0; j < cnt; j++) codes[e0 + j] = (uint16_t)f2h(a[j]);
-    }
-    if (reset) {
-        const float z[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-        store8<false>(acc, e0, cnt, z);
+        for (uint64_t e = row + threadIdx.x; e < n; e += kWG) {
+            codes[e] = (uint16_t)f2h(acc[e] / count);
+            if (reset) acc[e] = 0.0f;
+        }
     }
 }
 
@@ -1453,8 +1463,7 @@ hipError_t launch_reduce_fp16(const GroupTable &gt, uint64_t len, const ChainArg
 
 hipError_t launch_reduce_i8(const GroupTable &gt, uint64_t len, const ChainArgs &ca, hipStream_t s) {
     const dim3 grid(grid_for(len, (uint64_t)kI8Block * (kWG / 64)), gt.n_groups);
-    if (largest_group(gt) <= kSmallGroup) DEDLOC_LAUNCH(grid, reduce_i8_kernel<(int)kSmallGroup>, s, gt, len, ca);
-    DEDLOC_LAUNCH(grid, reduce_i8_kernel<DEDLOC_I8_BATCH>, s, gt, len, ca);
+    DEDLOC_LAUNCH(grid, reduce_i8_kernel<kI8Batch>, s, gt, len, ca);
 }
 
 hipError_t launch_lamb_a(int src, const Chunk &ch, uint32_t n_groups, const PeerTable &pt, const GradArgs &ga,

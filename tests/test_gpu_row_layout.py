@@ -1,0 +1,50 @@
+"""The elementwise kernels' rows of 2048 elements (GPU): lengths at the edges
+of a row and of a wave's 512, against the oracle, bit for bit, with the bytes
+past the end untouched."""
+
+import numpy as np
+import pytest
+
+import oracle
+from paper_2106_10207_amd import dedloc as D
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+LENGTHS = [1, 3, 511, 513, 2047, 2048, 2049, 4096, 3 * 2048 + 257]
+
+
+@pytest.mark.parametrize("n", LENGTHS)
+def test_rows(n):
+    print(f"\n[rows] {n}", flush=True)
+    rng = np.random.default_rng(n)
+    g = (rng.standard_normal(n) * 1e-2).astype(np.float32)
+    acc = rng.standard_normal(n).astype(np.float32)
+    want = oracle.encode_fp16(g)
+    pad = 16  # room past the end
+    up = lambda a: torch.from_numpy(a).cuda()
+    codes = torch.full((n + pad,), 0x1234, dtype=torch.int16, device="cuda")
+    D.dedloc_encode(up(g), D.DEDLOC_CODEC_FP16, codes=codes)
+    back = torch.full((n + pad,), 7.0, device="cuda")
+    D.dedloc_decode(codes, None, n, D.DEDLOC_CODEC_FP16, out=back)
+    back8 = torch.full((n + pad,), 7.0, device="cuda")
+    c8, s8 = oracle.encode_i8(g, 1024)
+    D.dedloc_decode(up(c8), up(s8), n, D.DEDLOC_CODEC_I8, out=back8)
+    torch.cuda.synchronize()
+    got = codes.cpu().numpy()
+    assert np.array_equal(got[:n].view(np.uint16), want) and np.all(got[n:] == 0x1234)
+    got = back.cpu().numpy()
+    assert np.array_equal(got[:n], want.view(np.float16).astype(np.float32)) and np.all(got[n:] == 7.0)
+    got = back8.cpu().numpy()
+    assert np.array_equal(got[:n], c8.astype(np.float32) * np.repeat(s8, 1024)[:n]) and np.all(got[n:] == 7.0)
+    # fma(b, g, acc) and acc / count: products and sums of these are exact in float64
+    for grad, h in ((up(g), g), (up(want.view(np.int16)), want.view(np.float16).astype(np.float32))):
+        a = up(acc.copy())
+        D.dedloc_accumulate(a, grad, 3.0)
+        expect = (np.float64(3.0) * h + acc).astype(np.float32)
+        assert np.array_equal(a.cpu().numpy(), expect)
+        out = torch.full((n + pad,), 0x1234, dtype=torch.int16, device="cuda")
+        D.dedloc_finalize(a, 8, D.DEDLOC_CODEC_FP16, codes=out, reset=True)
+        o = out.cpu().numpy()
+        assert np.array_equal(o[:n].view(np.uint16), oracle.encode_fp16(expect / np.float32(8.0)))
+        assert np.all(o[n:] == 0x1234) and not np.any(a.cpu().numpy())
