@@ -226,7 +226,7 @@ int run_reduce(int32_t codec, const PeerList &pl, uint32_t lo, uint32_t hi, bool
 struct Plan {
     std::vector<Chunk> chunks;
     bool one_pass = false;  // LAMB in one pass (else the two passes)
-    bool nt = false;        // the two passes' non-temporal form
+    bool nt = false;        // LARS: non-temporal accesses to the state
     size_t ws_part = 0, ws_trust = 0, ws_total = 0;
 };
 
@@ -248,19 +248,23 @@ int check_tensors(uint64_t P, const uint64_t *off, uint32_t T) {
 // moves 28 instead of 40 bytes of state per element, but its persistent grid
 // and the wait for every tensor's ratio cost more than that saves on small
 // vectors and on tables of many small tensors.  Measured, one pass against
-// two: 2M elements in 20 tensors 21.0 / 19.2 us, 4M in one 28.7 / 30.6, 8M in
-// 20 49.9 / 55.7; 4M in 200 52 / 41, 9M in 300 138 / 122 (12 peers), 17.7M in
-// 25 98 / 123, 2^30 in 1024 8.7 / 10.3 ms (8 peers).
-constexpr uint64_t kOnePassElements = 1ull << 23;
+// two, steps: 2M elements in 20 tensors 21.0 / 19.2 us, 4M in one 28.7 / 30.6, 8M
+// in 20 49.9 / 55.7, 4M in 200 52 / 41, 17.7M in 25 98 / 123.  Rounds: 9M in 5
+// (int8) 88.0 / 98.6, 9M in 300 138 / 122, 9M in 12 80.8 / 78.6, 12M in one 99.9 /
+// 98.9, 17M in 12 140.6 / 144.8, 20M in 30 162 / 171, 2^30 in 1024 8.9 / 10.1 ms.
+constexpr uint64_t kOnePassElements = 1ull << 23;       // a message or fp32 gradient
+constexpr uint64_t kOnePassElementsPeers = 1ull << 24;  // the fused average
 constexpr uint64_t kOnePassPerTensor = 1ull << 18;
-// The two passes' state beyond what the Infinity Cache keeps (x and v or m of
-// 2^23 elements are 64 MB of its 256): non-temporal accesses.
-constexpr uint64_t kNtElements = 1ull << 23;
+// LARS: x and v of 2^24 elements are 128 MB, half of the Infinity Cache.
+// Non-temporal accesses beyond: 8.5M and 9M elements 61.6 / 65.0 and 75.2 / 78.0
+// us, 12M equal, 18M 148.6 / 141.8, 26M 201.5 / 198.1, 40M 232.5 / 222.5
+// (without / with).
+constexpr uint64_t kNtElements = 1ull << 24;
 
-void make_plan(int opt, uint64_t P, const uint64_t *off, const uint8_t *flags, uint32_t T, Plan &pl) {
+void make_plan(int opt, bool peers, uint64_t P, const uint64_t *off, const uint8_t *flags, uint32_t T, Plan &pl) {
     uint64_t full = 0;  // tensors with elements
     for (uint32_t t = 0; t < T; t++) full += off[t + 1] > off[t];
-    pl.one_pass = opt == kOptLamb && P >= kOnePassElements && P / full >= kOnePassPerTensor;
+    pl.one_pass = opt == kOptLamb && P >= (peers ? kOnePassElementsPeers : kOnePassElements) && P / full >= kOnePassPerTensor;
     pl.nt = P >= kNtElements;
     const uint32_t per = pl.one_pass ? 2 : 1;  // rows per work item
     pl.chunks.clear();
@@ -438,7 +442,7 @@ int run_opt(int opt, int src_a, int src_b, const Plan &pl, const PeerTable *peer
             e = timed(k_b, s, [&] { return launch_lamb_b(ch, rt, n_check, op, x, m, v, w, nonce, trust_out, s); });
         } else {
             const TileWs w = carve_tiles(pl, ws);
-            e = timed(k_a, s, [&] { return launch_opt_a(opt, src_a, pl.nt, ch, pt, ga_a, op, x, m, v, w, s); });
+            e = timed(k_a, s, [&] { return launch_opt_a(opt, src_a, ch, pt, ga_a, op, x, m, v, w, s); });
             if (e != hipSuccess) return hip_fail(e, "optimizer pass A launch");
             e = timed(k_b, s, [&] {
                 return launch_opt_b(opt, src_b, pl.nt, ch, ga_b, op, x, m, v, w, nonce, trust_out, s);
@@ -458,7 +462,7 @@ int prepare_step(int opt, float *x, float *m, float *v, const void *grad, const 
     rc = check_tensors(P, offsets, n_tensors);
     if (rc) return rc;
     if (!flags) return fail(DEDLOC_ERR_INVALID_ARG, "flags must not be NULL");
-    make_plan(opt, P, offsets, flags, n_tensors, pl);
+    make_plan(opt, false, P, offsets, flags, n_tensors, pl);
     rc = check_state(opt, x, m, v, P, ws, ws_bytes, pl);
     if (rc) return rc;
     if (P == 0) return DEDLOC_OK;
@@ -501,7 +505,7 @@ int prepare_round(int opt, const void *const *peer_codes, const float *const *pe
     rc = check_tensors(P, offsets, n_tensors);
     if (rc) return rc;
     if (!flags) return fail(DEDLOC_ERR_INVALID_ARG, "flags must not be NULL");
-    make_plan(opt, P, offsets, flags, n_tensors, pl);
+    make_plan(opt, codec == DEDLOC_CODEC_FP16, P, offsets, flags, n_tensors, pl);
     rc = check_state(opt, x, m, v, P, ws, ws_bytes, pl, check_ws);
     if (rc) return rc;
     if (P == 0) return DEDLOC_OK;
@@ -709,7 +713,7 @@ int dedloc_reduce_shard(const void *const *peer_codes, const float *const *peer_
 size_t dedloc_lamb_workspace_bytes(uint64_t P, const uint64_t *offsets, uint32_t n_tensors) {
     if (check_tensors(P, offsets, n_tensors)) return 0;
     Plan pl;
-    make_plan(kOptLamb, P, offsets, nullptr, n_tensors, pl);
+    make_plan(kOptLamb, false, P, offsets, nullptr, n_tensors, pl);
     return pl.ws_total;
 }
 

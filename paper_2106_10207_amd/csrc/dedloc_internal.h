@@ -46,6 +46,7 @@ constexpr int kI8Block = 1024;         // int8 codec block = one wave64 x 16 cod
 constexpr int kI8PerLane = 16;
 // 60 peers' 8M elements: 4 83.5 us, 8 99.6, 12 90.1, 16 88.9; 4 also leaves room for 8 waves a SIMD
 constexpr int kI8Batch = DEDLOC_I8_BATCH;
+constexpr int kI8FewWaves = 16;  // where few waves are in flight
 constexpr int kChunkTensors = 192;     // tensors described per LAMB launch
 
 // Active peers (counts > 0) in ascending peer order, with their weights.
@@ -181,7 +182,7 @@ hipError_t launch_lamb_a(int src, const Chunk &ch, uint32_t n_groups, const Peer
                          float *trust_out, hipStream_t s);
 hipError_t launch_lamb_b(const Chunk &ch, const RestTable &rt, uint32_t n_check, const OptParams &op, float *x, float *m,
                          float *v, const LineWs &ws, uint32_t nonce, float *trust_out, hipStream_t s);
-hipError_t launch_opt_a(int opt, int src, bool nt, const Chunk &ch, const PeerTable &p, const GradArgs &ga,
+hipError_t launch_opt_a(int opt, int src, const Chunk &ch, const PeerTable &p, const GradArgs &ga,
                         const OptParams &op, float *x, float *m, float *v, const TileWs &ws, hipStream_t s);
 hipError_t launch_opt_b(int opt, int src, bool nt, const Chunk &ch, const GradArgs &ga, const OptParams &op, float *x,
                         float *m, float *v, const TileWs &ws, uint32_t nonce, float *trust_out, hipStream_t s);

@@ -628,11 +628,12 @@ __device__ __forceinline__ float trust_ratio(uint8_t flags, const OptParams &op,
 // Pass A: gradient (optionally the fused average), for LAMB the new moments,
 // and the per-tile sums of x^2 and u^2 (LARS: g^2), in fp64 with a fixed tree
 // inside the tile; pass B: the ratios and the update, from memory again.
-// NT: non-temporal accesses for the state that no other pass of the call
-// reads again, for vectors that the 256 MB Infinity Cache does not keep from
-// one call to the next (ResNet-50, 32 peers, LARS: 419 -> 406 us; on 6M
-// elements, which it keeps, 31.2 -> 33.6 us: the caller chooses by size).
-template <int SRC, int OPT, bool NT>
+// NT (LARS's pass B): non-temporal accesses for state that the 256 MB Infinity
+// Cache does not keep from one call to the next (ResNet-50, 32 peers: 419 ->
+// 412 us, 40M elements 232 -> 222; on 6M, which it keeps, 31.2 -> 33.6: the
+// caller chooses by size).  LAMB's passes were slower with them (60M elements
+// in 400 tensors 606 -> 631 us: pass B finds part of x, m', v' in the cache).
+template <int SRC, int OPT>
 __global__ __launch_bounds__(kWG) void opt_a_kernel(const Chunk ch, const PeerTable pt, const GradArgs ga,
                                                     const OptParams op, const float *__restrict__ x,
                                                     float *__restrict__ m, float *__restrict__ v, TileWs ws) {
@@ -649,8 +650,8 @@ __global__ __launch_bounds__(kWG) void opt_a_kernel(const Chunk ch, const PeerTa
         load8<false>(x, e0, cnt, xv);
         if (OPT == kOptLamb) {
             float mv[8], vv[8];
-            load8<NT>(m, e0, cnt, mv);
-            load8<NT>(v, e0, cnt, vv);
+            load8<false>(m, e0, cnt, mv);
+            load8<false>(v, e0, cnt, vv);
             load_grad<SRC, kPeerBatch>(ga, pt, e0, cnt, g);
 #pragma unroll
             for (int j = 0; j < 8; j++) {
@@ -1463,6 +1464,15 @@ hipError_t launch_reduce_fp16(const GroupTable &gt, uint64_t len, const ChainArg
 
 hipError_t launch_reduce_i8(const GroupTable &gt, uint64_t len, const ChainArgs &ca, hipStream_t s) {
     const dim3 grid(grid_for(len, (uint64_t)kI8Block * (kWG / 64)), gt.n_groups);
+    // Few waves (under 16 a CU) and many peers: the serial chain of batches is
+    // what the launch takes, so the loads go out 16 at a time (30 peers: 1M
+    // elements 31.9 us a round against 37.0, 3M 48.7 / 50.7; 6M the other way
+    // round 77.7 / 73.1).  Also where batches of 4, of which 32 waves a CU run at
+    // once, leave a second generation nearly empty (10.5M elements 120.7 us
+    // against 125.7; 13M 169.3 / 168.0, 8M 88.8 / 84.1).
+    const uint64_t groups = (uint64_t)grid.x * grid.y, at_once = 256 * 8;
+    if (largest_group(gt) > 12 && (groups < at_once / 2 || (groups > at_once && groups <= at_once * 3 / 2)))
+        DEDLOC_LAUNCH(grid, reduce_i8_kernel<kI8FewWaves>, s, gt, len, ca);
     DEDLOC_LAUNCH(grid, reduce_i8_kernel<kI8Batch>, s, gt, len, ca);
 }
 
@@ -1489,13 +1499,13 @@ hipError_t launch_lamb_b(const Chunk &ch, const RestTable &rt, uint32_t n_check,
     DEDLOC_LAUNCH(dim3(rt.n_rest + n_check), lamb_b_kernel, s, ch, rt, op, x, m, v, ws, nonce, trust_out);
 }
 
-template <int OPT, bool NT>
+template <int OPT>
 static hipError_t launch_a(int src, const Chunk &ch, const PeerTable &p, const GradArgs &ga, const OptParams &op,
                            float *x, float *m, float *v, const TileWs &ws, hipStream_t s) {
     const dim3 g(ch.begin[ch.nt]);
     switch (src) {
 #define DEDLOC_CASE(SRC) \
-    case SRC: DEDLOC_LAUNCH(g, (opt_a_kernel<SRC, OPT, NT>), s, ch, p, ga, op, x, m, v, ws)
+    case SRC: DEDLOC_LAUNCH(g, (opt_a_kernel<SRC, OPT>), s, ch, p, ga, op, x, m, v, ws)
     DEDLOC_CASE(kSrcF32);
     DEDLOC_CASE(kSrcFP16);
     DEDLOC_CASE(kSrcI8);
@@ -1507,21 +1517,16 @@ static hipError_t launch_a(int src, const Chunk &ch, const PeerTable &p, const G
     }
 }
 
-hipError_t launch_opt_a(int opt, int src, bool nt, const Chunk &ch, const PeerTable &p, const GradArgs &ga,
-                        const OptParams &op, float *x, float *m, float *v, const TileWs &ws, hipStream_t s) {
-    if (opt == kOptLamb)
-        return nt ? launch_a<kOptLamb, true>(src, ch, p, ga, op, x, m, v, ws, s)
-                  : launch_a<kOptLamb, false>(src, ch, p, ga, op, x, m, v, ws, s);
-    // LARS's pass A reads and keeps only x: no non-temporal form of its own
-    return launch_a<kOptLars, false>(src, ch, p, ga, op, x, m, v, ws, s);
+hipError_t launch_opt_a(int opt, int src, const Chunk &ch, const PeerTable &p, const GradArgs &ga, const OptParams &op,
+                        float *x, float *m, float *v, const TileWs &ws, hipStream_t s) {
+    return opt == kOptLamb ? launch_a<kOptLamb>(src, ch, p, ga, op, x, m, v, ws, s)
+                           : launch_a<kOptLars>(src, ch, p, ga, op, x, m, v, ws, s);
 }
 
 template <bool NT>
-static hipError_t launch_b(int opt, int src, const Chunk &ch, const GradArgs &ga, const OptParams &op, float *x,
-                           float *m, float *v, const TileWs &ws, uint32_t nonce, float *trust_out, hipStream_t s) {
-    const dim3 g(ch.nt + ch.begin[ch.nt]);  // one producer per tensor, then every tile
-    if (opt == kOptLamb)
-        DEDLOC_LAUNCH(g, (opt_b_kernel<kSrcF32, kOptLamb, NT>), s, ch, ga, op, x, m, v, ws, nonce, trust_out);
+static hipError_t launch_lars_b(int src, dim3 g, const Chunk &ch, const GradArgs &ga, const OptParams &op, float *x,
+                                float *v, const TileWs &ws, uint32_t nonce, float *trust_out, hipStream_t s) {
+    float *m = nullptr;
     switch (src) {
     case kSrcF32: DEDLOC_LAUNCH(g, (opt_b_kernel<kSrcF32, kOptLars, NT>), s, ch, ga, op, x, m, v, ws, nonce, trust_out);
     case kSrcFP16: DEDLOC_LAUNCH(g, (opt_b_kernel<kSrcFP16, kOptLars, NT>), s, ch, ga, op, x, m, v, ws, nonce, trust_out);
@@ -1532,8 +1537,11 @@ static hipError_t launch_b(int opt, int src, const Chunk &ch, const GradArgs &ga
 
 hipError_t launch_opt_b(int opt, int src, bool nt, const Chunk &ch, const GradArgs &ga, const OptParams &op, float *x,
                         float *m, float *v, const TileWs &ws, uint32_t nonce, float *trust_out, hipStream_t s) {
-    return nt ? launch_b<true>(opt, src, ch, ga, op, x, m, v, ws, nonce, trust_out, s)
-              : launch_b<false>(opt, src, ch, ga, op, x, m, v, ws, nonce, trust_out, s);
+    const dim3 g(ch.nt + ch.begin[ch.nt]);  // one producer per tensor, then every tile
+    if (opt == kOptLamb)
+        DEDLOC_LAUNCH(g, (opt_b_kernel<kSrcF32, kOptLamb, false>), s, ch, ga, op, x, m, v, ws, nonce, trust_out);
+    return nt ? launch_lars_b<true>(src, g, ch, ga, op, x, v, ws, nonce, trust_out, s)
+              : launch_lars_b<false>(src, g, ch, ga, op, x, v, ws, nonce, trust_out, s);
 }
 
 hipError_t launch_accumulate(float *acc, const void *grad, bool fp16, uint64_t n, float b, hipStream_t s) {

@@ -29,6 +29,11 @@ TABLES = {
 }
 
 
+# a round of fp16 messages takes the pass at twice that size
+ROUND_TABLES = {k: [2 * SMALLEST if n == SMALLEST else n for n in TABLES[k]] for k in ("smallest", "ragged")}
+ROUND_TABLES["edges"] = EDGES + [2 * SMALLEST]
+
+
 def _inputs(sizes, src, seed=3):
     off = np.concatenate([[0], np.cumsum(sizes)]).astype(np.uint64)
     P = int(off[-1])
@@ -94,7 +99,7 @@ def test_one_pass_round(table, n_peers, local):
     """The fused average inside the pass (66 peers: its chained form), bit for
     bit against the average and the step called one after the other."""
     print(f"\n[one pass] round {table} {n_peers} {local}", flush=True)
-    off, flags, x, m, v, g, _, _ = _inputs(TABLES[table], "f32")
+    off, flags, x, m, v, g, _, _ = _inputs(ROUND_TABLES[table], "f32")
     P = x.numel()
     counts = np.arange(1, n_peers + 1, dtype=np.uint32)
     codes = [D.dedloc_encode(torch.roll(g, 8 * p), D.DEDLOC_CODEC_FP16)[0] for p in range(n_peers)]
