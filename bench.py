@@ -80,16 +80,26 @@ KERNEL_KINDS = {
     "void dedloc::opt_a_kernel<3, 0>": "lamb_a_fused_fp16",
     "void dedloc::opt_a_kernel<4, 0>": "lamb_a_fused_fp16",
     "void dedloc::opt_a_kernel<5, 0>": "lamb_a_fused_fp16",
-    "void dedloc::opt_b_kernel<0, 0>": "lamb_b",
+    "void dedloc::opt_b_kernel<0, 0, false>": "lamb_b",
+    "void dedloc::lamb_a_kernel<0>": "lamb_a_f32",
+    "void dedloc::lamb_a_kernel<1>": "lamb_a_fp16",
+    "void dedloc::lamb_a_kernel<2>": "lamb_a_i8",
+    "void dedloc::lamb_a_kernel<3>": "lamb_a_fused_fp16",
+    "void dedloc::lamb_a_kernel<4>": "lamb_a_fused_fp16",
+    "void dedloc::lamb_a_kernel<5>": "lamb_a_fused_fp16",
+    "dedloc::lamb_b_kernel": "lamb_b",
     "void dedloc::opt_a_kernel<0, 1>": "lars_a_f32",
     "void dedloc::opt_a_kernel<1, 1>": "lars_a_fp16",
     "void dedloc::opt_a_kernel<2, 1>": "lars_a_i8",
     "void dedloc::opt_a_kernel<3, 1>": "lars_a_fused_fp16",
     "void dedloc::opt_a_kernel<4, 1>": "lars_a_fused_fp16",
     "void dedloc::opt_a_kernel<5, 1>": "lars_a_fused_fp16",
-    "void dedloc::opt_b_kernel<0, 1>": "lars_b",
-    "void dedloc::opt_b_kernel<1, 1>": "lars_b",
-    "void dedloc::opt_b_kernel<2, 1>": "lars_b",
+    "void dedloc::opt_b_kernel<0, 1, false>": "lars_b",
+    "void dedloc::opt_b_kernel<0, 1, true>": "lars_b",
+    "void dedloc::opt_b_kernel<1, 1, false>": "lars_b",
+    "void dedloc::opt_b_kernel<1, 1, true>": "lars_b",
+    "void dedloc::opt_b_kernel<2, 1, false>": "lars_b",
+    "void dedloc::opt_b_kernel<2, 1, true>": "lars_b",
     "void dedloc::accumulate_kernel<false>": "accumulate",
     "void dedloc::accumulate_kernel<true>": "accumulate_fp16",
     "dedloc::finalize_fp16_kernel": "finalize_fp16",
@@ -199,14 +209,29 @@ def summarize_trace(root_dir, workload, extra=""):
     return out
 
 
+def _one_pass_held(wl):
+    """Elements whose x and u a LAMB round of `wl` holds on chip until the trust
+    ratio is known (their x' is written by the first pass), or None where the
+    round runs as two passes.  The library's rule: enough elements, in
+    tensors large enough; at most 2 x 768 units of 4096 elements are held of
+    one tensor."""
+    sizes = np.diff(np.asarray(wl.offsets()).astype(np.int64))
+    least = 1 << (24 if wl.codec == "fp16" else 23)
+    if wl.P < least or wl.P // max(1, int(np.count_nonzero(sizes))) < 1 << 18:
+        return None
+    return int(np.minimum(sizes, 2 * 768 * 4096).sum())
+
+
 def _instance(kind, dr):
     """rocprofv3's name of the kernel instance a step of `dr` launches for `kind`."""
     src = 5 if dr.local_in_kernel else (4 if int(np.count_nonzero(dr.counts)) > 64 else 3)
-    names = {"lamb_a_fused_fp16": f"void dedloc::opt_a_kernel<{src}, 0>",
+    held = _one_pass_held(dr.wl) is not None
+    names = {"lamb_a_fused_fp16": f"void dedloc::lamb_a_kernel<{src}>" if held else
+                                  f"void dedloc::opt_a_kernel<{src}, 0>",
              "lars_a_fused_fp16": f"void dedloc::opt_a_kernel<{src}, 1>",
-             "reduce_i8": "void dedloc::reduce_i8_kernel<16>",
-             "lamb_b": "void dedloc::opt_b_kernel<0, 0>",
-             "lamb_a_i8": "void dedloc::opt_a_kernel<2, 0>"}
+             "reduce_i8": "void dedloc::reduce_i8_kernel<4>",
+             "lamb_b": "dedloc::lamb_b_kernel" if held else "void dedloc::opt_b_kernel<0, 0, false>",
+             "lamb_a_i8": "void dedloc::lamb_a_kernel<2>" if held else "void dedloc::opt_a_kernel<2, 0>"}
     return names.get(kind)
 
 
@@ -240,6 +265,8 @@ def kernel_roofline(dr, prof, steps):
       reduce_i8:         N*b*P peer reads + b*P code/scale writes
       lamb_a_i8:         b*P code reads + 20P (x, m, v reads; m', v' writes)
       lamb_b:            12P reads (x, m', v') + 4P writes
+      (LAMB in one pass: lamb_a also writes x' of the H elements it holds on
+      chip, +4H, and lamb_b moves its 16 bytes for the other P - H only)
       lars_a_fused_fp16: N*b*P peer reads + b*P code writes + 4P reads of x
       lars_a_i8:         b*P code reads + 4P reads of x
       lars_b:            b*P code reads + 8P reads (x, v) + 8P writes (x', v')
@@ -249,12 +276,13 @@ def kernel_roofline(dr, prof, steps):
     b = wl.wire_bytes_per_elem
     n_act = int(np.count_nonzero(dr.counts))
     loc = 4.0 if dr.local_in_kernel else 0.0
+    held = _one_pass_held(wl) or 0
     per_launch = {
-        "lamb_a_fused_fp16": (n_act * b + b + 20.0 + loc) * P,
+        "lamb_a_fused_fp16": (n_act * b + b + 20.0 + loc) * P + 4.0 * held,
         "reduce_i8": (n_act * b + b) * P,
-        "lamb_a_i8": (b + 20.0) * P,
-        "lamb_a_fp16": (b + 20.0) * P,
-        "lamb_b": 16.0 * P,
+        "lamb_a_i8": (b + 20.0) * P + 4.0 * held,
+        "lamb_a_fp16": (b + 20.0) * P + 4.0 * held,
+        "lamb_b": 16.0 * (P - held),
         "lars_a_fused_fp16": (n_act * b + b + 4.0 + loc) * P,
         "lars_a_i8": (b + 4.0) * P,
         "lars_a_fp16": (b + 4.0) * P,
