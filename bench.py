@@ -389,8 +389,10 @@ def bench_balance():
 def bench_group(args, wl):
     """Group (Moshpit) all-reduce of the workload's peer messages in groups
     of --group-size: ceil(log_m n) iterations, one launch each.  Algorithmic
-    bytes per iteration: every member's message read once (N_k * P * b) and
-    every group message written once (G_k * P * b)."""
+    bytes per iteration, over the groups whose members differ from every other
+    group's (the others' average is the same message): every member's message
+    read once and the group message written once, in the last iteration once
+    for every output."""
     import torch
     from paper_2106_10207_amd import dedloc as D
     from paper_2106_10207_amd import harness as H
@@ -411,8 +413,9 @@ def bench_group(args, wl):
             base = (g // lo) * lo * m + (g % lo)
             members = [base + j * lo for j in range(m)]
             tot = sum(cnt[s] for s in members)
-            reads += sum(1 for s in members if cnt[s] > 0)
-            writes += 1 if tot > 0 else 0
+            if g % lo == 0:  # ids equal but for g % lo average the same messages
+                reads += sum(1 for s in members if cnt[s] > 0)
+                writes += (m ** d // m if k == d - 1 else 1) if tot > 0 else 0
             for s in members:
                 new[s] = tot
         cnt = new
