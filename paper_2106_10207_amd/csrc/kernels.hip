@@ -323,13 +323,20 @@ __device__ __forceinline__ float reduce_fp16_one(const PeerTable &pt, uint32_t p
 // message and their decoded values averaged like any peer's.  (Issuing the
 // next peers' loads before the local peer's values are used measured the
 // same, and keeping the local loads inside a peer batch costs registers.)
-template <int B>
+// NT: the gradient's loads carry the non-temporal hint.  Chosen per kernel that
+// calls it, by times per round with the hint / without, three sets of buffers
+// in turn and the same set again and again.  LAMB's pass A, ResNet-50: 32 peers
+// 500 / 503 and 437 / 462 us, 16 peers 335 / 339 and 285 / 305; LARS' pass A,
+// 32 peers: 415 / 418 and 413 / 399; reduce_fp16_kernel, ALBERT-large's round of
+// 100 peers: 798 / 810 and 783 / 771, ResNet-50's 1220 / 1214 and 1153 / 1177.
+// lamb_a_kernel, which has 4 peer loads in flight and not 16: ALBERT-large, the
+// same set again, 207 / 198 (the two halves of each 32 bytes are fetched apart).
+template <int B, bool NT>
 __device__ __forceinline__ void reduce_fp16x8_local(const PeerTable &pt, uint32_t n, uint32_t lp,
                                                     const LocalArgs &la, uint64_t e0, float *acc) {
     reduce_fp16x8<B>(pt, 0, lp, e0, acc);
-    // plain loads: the two halves of each 32 bytes would otherwise be fetched
-    // apart (ALBERT-large's round 207 instead of 198 us)
-    const f32x4 ga = *(const f32x4 *)(la.grad + e0), gb = *(const f32x4 *)(la.grad + e0 + 4);
+    const f32x4 *q = (const f32x4 *)(la.grad + e0);
+    const f32x4 ga = NT ? ld_stream(q) : q[0], gb = NT ? ld_stream(q + 1) : q[1];
     const float v[8] = {ga[0], ga[1], ga[2], ga[3], gb[0], gb[1], gb[2], gb[3]};
     const u32x4 lc = pack_fp16x8(v);
     st_msg((u32x4 *)((uint16_t *)la.codes + e0), lc);
@@ -366,7 +373,7 @@ __global__ __launch_bounds__(kWG) void reduce_fp16_kernel(const GroupTable gt, u
     if (e0 + kVec <= len) {
         float acc[8];
         init8(ca.acc_in, e0, acc);
-        if (local) reduce_fp16x8_local<B>(gt.pt, p_hi, ca.local.pos, ca.local, e0, acc);
+        if (local) reduce_fp16x8_local<B, true>(gt.pt, p_hi, ca.local.pos, ca.local, e0, acc);
         else reduce_fp16x8<B>(gt.pt, p_lo, p_hi, e0, acc);
         if (ca.final_pass) {
             const u32x4 c = pack_fp16x8(acc);
@@ -512,8 +519,9 @@ __device__ __forceinline__ uint32_t chunk_tensor(const Chunk &ch, uint32_t b) {
     return lo;
 }
 
-// Gradient of the elements [e0, e0+cnt), cnt <= 8, for source SRC.
-template <int SRC, int B>
+// Gradient of the elements [e0, e0+cnt), cnt <= 8, for source SRC (NT: as
+// for reduce_fp16x8_local).
+template <int SRC, int B, bool NT>
 __device__ __forceinline__ void load_grad(const GradArgs &ga, const PeerTable &pt, uint64_t e0,
                                           int cnt, float *g) {
     if (cnt == kVec) {
@@ -532,7 +540,7 @@ __device__ __forceinline__ void load_grad(const GradArgs &ga, const PeerTable &p
         } else {
             float acc[8];
             init8(SRC == kSrcPeersFP16Chain ? ga.acc_in : nullptr, e0, acc);
-            if (SRC != kSrcPeersFP16 && ga.local.pos >= 0) reduce_fp16x8_local<B>(pt, pt.n, ga.local.pos, ga.local, e0, acc);
+            if (SRC != kSrcPeersFP16 && ga.local.pos >= 0) reduce_fp16x8_local<B, NT>(pt, pt.n, ga.local.pos, ga.local, e0, acc);
             else reduce_fp16x8<B>(pt, 0, pt.n, e0, acc);
             const u32x4 c = pack_fp16x8(acc);
             st_msg((u32x4 *)(ga.out_codes + e0), c);
@@ -652,7 +660,7 @@ __global__ __launch_bounds__(kWG) void opt_a_kernel(const Chunk ch, const PeerTa
             float mv[8], vv[8];
             load8<false>(m, e0, cnt, mv);
             load8<false>(v, e0, cnt, vv);
-            load_grad<SRC, kPeerBatch>(ga, pt, e0, cnt, g);
+            load_grad<SRC, kPeerBatch, OPT == kOptLamb>(ga, pt, e0, cnt, g);
 #pragma unroll
             for (int j = 0; j < 8; j++) {
                 const float mn = fmaf(op.beta1, mv[j], op.omb1 * g[j]);
@@ -668,7 +676,7 @@ __global__ __launch_bounds__(kWG) void opt_a_kernel(const Chunk ch, const PeerTa
             store8<false>(m, e0, cnt, mv);
             store8<false>(v, e0, cnt, vv);
         } else {
-            load_grad<SRC, kPeerBatch>(ga, pt, e0, cnt, g);
+            load_grad<SRC, kPeerBatch, OPT == kOptLamb>(ga, pt, e0, cnt, g);
 #pragma unroll
             for (int j = 0; j < 8; j++) {
                 if (j < cnt) {
@@ -816,7 +824,7 @@ __global__ __launch_bounds__(kWG) void opt_b_kernel(const Chunk ch, const GradAr
             for (int j = 0; j < 8; j++) dv[j] = lamb_dir(mv[j], vv[j], xv[j], lam, op);
         } else {
             float g[8];
-            load_grad<SRC, kPeerBatch>(ga, PeerTable{}, e0, cnt, g);
+            load_grad<SRC, kPeerBatch, true>(ga, PeerTable{}, e0, cnt, g);
 #pragma unroll
             for (int j = 0; j < 8; j++) dv[j] = g[j] + lam * xv[j];
         }
@@ -1129,7 +1137,7 @@ __global__ __launch_bounds__(kWG, kLineGroups) void lamb_a_kernel(const Chunk ch
         if (kPeers ? r.e0() < r.t_hi : r.row < r.t_hi) {
             const float lam = (ch.flags[t.k] & 1u) ? op.wd : 0.0f;
             float g[8], mv[8], vv[8];
-            if constexpr (kPeers) load_grad<SRC, kLinePeerBatch>(ga, pt, r.e0(), count8(r.e0(), r.t_hi), g);
+            if constexpr (kPeers) load_grad<SRC, kLinePeerBatch, false>(ga, pt, r.e0(), count8(r.e0(), r.t_hi), g);
             else fg.decode(g);
 #pragma unroll
             for (int j = 0; j < 8; j++) {
