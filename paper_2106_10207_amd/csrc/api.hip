@@ -426,12 +426,13 @@ int run_opt(int opt, int src_a, int src_b, const Plan &pl, const PeerTable *peer
         if (pl.one_pass) {
             const LineWs w = carve_line(pl, ws);
             const uint32_t units = ch.begin[ch.nt];
-            e = timed(k_a, s, [&] {
-                return launch_lamb_a(src_a, ch, std::min(units, groups), pt, ga_a, op, x, m, v, w, nonce, trust_out, s);
-            });
-            if (e != hipSuccess) return hip_fail(e, "optimizer pass A launch");
             RestTable rt;
             memset(&rt, 0, sizeof rt);
+            rt.grid_a = std::min(units, groups);
+            e = timed(k_a, s, [&] {
+                return launch_lamb_a(src_a, ch, rt.grid_a, pt, ga_a, op, x, m, v, w, nonce, trust_out, s);
+            });
+            if (e != hipSuccess) return hip_fail(e, "optimizer pass A launch");
             for (uint32_t k = 0; k < ch.nt; k++) {
                 const uint32_t n = ch.begin[k + 1] - ch.begin[k];
                 rt.begin[k] = rt.n_rest;

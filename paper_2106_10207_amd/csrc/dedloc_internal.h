@@ -111,11 +111,13 @@ struct Chunk {
     uint8_t flags[kChunkTensors];
 };
 
-// The rows of a chunk that LAMB's one pass does not hold on chip: tensor k
-// owns workgroups [begin[k], begin[k+1]) of the pass after it [begin[k], begin[k+1]).
+// The rows of a chunk that LAMB's one pass does not hold on chip: those of
+// tensor k are workgroups [begin[k], begin[k+1]) of the pass after it, counted
+// from its last.
 struct RestTable {
     uint32_t begin[kChunkTensors + 1];
     uint32_t n_rest;  // begin[nt]
+    uint32_t grid_a;  // workgroups of the one pass
 };
 
 // Optimizer applied after the gather.
@@ -165,7 +167,7 @@ struct TileWs {
 struct LineWs {
     uint32_t *epoch;             // [0]: read by pass A, advanced by pass B; [1]: pass A's value for pass B
     uint32_t *gave_up;           // the tag if any tensor of the launch was given up
-    unsigned long long *part;    // 16 bytes per row: the partial sums
+    unsigned long long *part;    // 16 bytes per row: records of partial sums
     unsigned long long *trust;   // per tensor: (tag << 32) | bits of r_t
 };
 

@@ -946,10 +946,10 @@ struct RawGrad {
     }
 };
 
-// Partial sums of a unit (x^2 and u^2) as four words, each half of a
-// double under the call's tag: whoever reads a word sees from it alone
-// whether this launch wrote it, so no ordering between two locations (a
-// release fence: on gfx950 a full L2 write-back) is needed.
+// Partial sums (x^2 and u^2) as four words, each half of a double under the
+// call's tag: whoever reads a word sees from it alone whether this launch
+// wrote it, so no ordering between two locations (a release fence: on gfx950
+// a full L2 write-back) is needed.
 __device__ __forceinline__ void put_part(unsigned long long *w, uint32_t tag, double a, double b) {
     const unsigned long long t = (unsigned long long)tag << 32;
     const unsigned long long ab = (unsigned long long)__double_as_longlong(a);
@@ -960,7 +960,7 @@ __device__ __forceinline__ void put_part(unsigned long long *w, uint32_t tag, do
     __hip_atomic_store(w + 3, t | (bb >> 32), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// A unit's sums, and whether all four words carry the tag.
+// The sums of a record, and whether all four words carry the tag.
 __device__ __forceinline__ bool get_part(const unsigned long long *w, uint32_t tag, double &a, double &b) {
     unsigned long long q[4];
 #pragma unroll
@@ -975,8 +975,8 @@ __device__ __forceinline__ bool gave_up(const LineWs &ws, uint32_t tag) {
     return __hip_atomic_load(ws.gave_up, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == tag;
 }
 
-// The same, polling at most `polls` times more, and less once any tensor of
-// the launch was given up.
+// The sums of a record once it is there, polling at most `polls` times, and less
+// once any tensor of the launch was given up.
 __device__ __forceinline__ bool wait_part(const LineWs &ws, const unsigned long long *w, uint32_t tag, uint32_t polls,
                                           double &a, double &b) {
     for (uint32_t i = 0; i < polls; i++) {
@@ -987,21 +987,24 @@ __device__ __forceinline__ bool wait_part(const LineWs &ws, const unsigned long 
     return false;
 }
 
-// Sums over a tensor of the partials of its first n units (records from
-// `part` on), by the whole workgroup, in a fixed order: thread-strided, then
-// a fixed tree.  WAIT: poll for records not yet written (bounded); otherwise
-// all of them are there.  Returns whether every record was seen; thread 0
-// gets the sums.
+// Sums over a tensor of its records [0, n) from `part` on without number
+// `own`, by the whole workgroup, in a fixed order: thread-strided, then a
+// fixed tree.  At most three records a thread, since each workgroup of the grid
+// (three per CU) leaves one per tensor.  WAIT: poll for records not yet written
+// (bounded); otherwise all of them are there.  Returns whether every record was
+// seen; thread 0 gets the sums.
 template <bool WAIT>
-__device__ __forceinline__ bool unit_sums(const LineWs &ws, const unsigned long long *part, uint32_t n, uint32_t tag,
-                                          uint32_t polls, double &a0, double &a1) {
+__device__ __forceinline__ bool record_sums(const LineWs &ws, const unsigned long long *part, uint32_t n, uint32_t own,
+                                            uint32_t tag, uint32_t polls, double &a0, double &a1) {
     bool ok = true;
     a0 = 0.0;
     a1 = 0.0;
     for (uint32_t i = threadIdx.x; i < n && ok; i += kWG) {
-        double p, q;
-        if (WAIT) ok = wait_part(ws, part + 4 * (uint64_t)i, tag, polls, p, q);
-        else get_part(part + 4 * (uint64_t)i, tag, p, q);
+        double p = 0.0, q = 0.0;
+        if (i != own) {
+            if (WAIT) ok = wait_part(ws, part + 4 * (uint64_t)i, tag, polls, p, q);
+            else get_part(part + 4 * (uint64_t)i, tag, p, q);
+        }
         a0 += p;
         a1 += q;
     }
@@ -1027,12 +1030,22 @@ struct UnitAt {
     __device__ __forceinline__ bool held(const OptParams &op) const { return units - 1 - unit < op.hold; }
 };
 
-// The partials of tensor k: 16 bytes of workspace per row, which hold a
-// record of 32 bytes for every unit but the last, and the last one's two sums
-// untagged (the workgroup that owns it forms the ratio; pass B reads them
-// after the launch).
+// The records of tensor k, in its 16 bytes of workspace per row (32 per unit,
+// of which the last may have 16): one record of 32 bytes for each workgroup
+// that has units of it (record_of).  The workgroup of the last unit forms the
+// ratio and leaves its two sums untagged (pass B reads them after the launch).
+// A record per unit instead took the owner 2^e / 2^20 dependent reads on a
+// tensor of 2^e elements: longer than the others wait (2^28 elements 34 ms
+// instead of 1.9).
 __device__ __forceinline__ unsigned long long *tensor_parts(const Chunk &ch, const LineWs &ws, uint32_t k) {
     return ws.part + 2 * (uint64_t)(ch.row_base + 2 * ch.begin[k] - ch.odd_before[k]);
+}
+
+// Number of a workgroup's record: its unit's where no workgroup has two units
+// of the tensor, else its own (there are then more than G units, so number
+// G - 1 has 32 bytes).
+__device__ __forceinline__ uint32_t record_of(uint32_t unit, uint32_t units, uint32_t G, uint32_t group) {
+    return units > G ? group : unit;
 }
 
 // The word of a tensor decides for all of it: (tag << 32) | bits of r once
@@ -1085,7 +1098,6 @@ __global__ __launch_bounds__(kWG, kLineGroups) void lamb_a_kernel(const Chunk ch
     // the tag as pass B reads it (ws.epoch[0] is advanced there, and read
     // here only)
     if (blockIdx.x == 0 && threadIdx.x == 0) ws.epoch[1] = epoch;
-
     float xr[NR][8], dr[NR][8];
     uint32_t slot = 0, it = 0;  // slot: (it - NR) % NL
     auto unpark = [&](uint32_t sl, float *xp, float *dp) {
@@ -1156,17 +1168,19 @@ __global__ __launch_bounds__(kWG, kLineGroups) void lamb_a_kernel(const Chunk ch
         const bool more = half == 0 || b + G < n;
         const UnitAt tn = half == 0 || b + G >= n ? t : UnitAt(ch, b + G, t.k);
         if (more) fetch(half == 0 ? Row<GF>(r.row + kRow, r.t_hi) : Row<GF>(tn.row, tn.t_hi));
-        if (half == 1) {
+        if (half == 1 && t.unit + G >= t.units) {  // the workgroup's last unit of the tensor
             block_sum2(s0, s1);
+            const uint32_t rec = record_of(t.unit, t.units, G, blockIdx.x);
             unsigned long long *part = tensor_parts(ch, ws, t.k);
             if (t.unit != t.units - 1) {
-                if (threadIdx.x == 0) put_part(part + 4 * (uint64_t)t.unit, tag, s0, s1);
+                if (threadIdx.x == 0) put_part(part + 4 * (uint64_t)rec, tag, s0, s1);
             } else {
                 // the workgroup of the tensor's last unit publishes its ratio
                 double a0 = 0.0, a1 = 0.0;
-                const bool ok = t.units == 1 || unit_sums<true>(ws, part, t.units - 1, tag, op.trust_polls, a0, a1);
+                const uint32_t n_rec = t.units < G ? t.units : G;
+                const bool ok = n_rec == 1 || record_sums<true>(ws, part, n_rec, rec, tag, op.trust_polls, a0, a1);
                 if (threadIdx.x == 0) {
-                    double *own = (double *)(part + 4 * (uint64_t)t.unit);
+                    double *own = (double *)(part + 4 * (uint64_t)rec);
                     own[0] = s0;
                     own[1] = s1;
                     unsigned long long *word = ws.trust + ch.t0 + t.k;
@@ -1261,20 +1275,51 @@ __device__ __forceinline__ void redo_row(const OptParams &op, float *__restrict_
     r.store(x, xv);
 }
 
-// The ratio of tensor k after pass A: as decided, else from the partials.
-__device__ __forceinline__ float known_ratio(const Chunk &ch, const OptParams &op, const LineWs &ws, uint32_t k,
-                                             uint32_t tag) {
-    const unsigned long long w = ws.trust[ch.t0 + k];
-    if ((uint32_t)(w >> 32) == tag && (uint32_t)w != kFailed) return __uint_as_float((uint32_t)w);
-    const uint32_t last = ch.begin[k + 1] - ch.begin[k] - 1;
+// The ratio of tensor k, which pass A gave up, from its records; G: pass A's grid.
+__device__ __forceinline__ float settled_ratio(const Chunk &ch, const OptParams &op, const LineWs &ws, uint32_t k,
+                                               uint32_t G, uint32_t tag) {
+    const uint32_t units = ch.begin[k + 1] - ch.begin[k];
+    const uint32_t n_rec = units < G ? units : G, own_rec = record_of(units - 1, units, G, (ch.begin[k + 1] - 1) % G);
     const unsigned long long *part = tensor_parts(ch, ws, k);
-    const double *own = (const double *)(part + 4 * (uint64_t)last);
+    const double *own = (const double *)(part + 4 * (uint64_t)own_rec);
     __shared__ float s_r;
     double a0, a1;
-    unit_sums<false>(ws, part, last, tag, 0, a0, a1);
+    record_sums<false>(ws, part, n_rec, own_rec, tag, 0, a0, a1);
     if (threadIdx.x == 0) s_r = trust_ratio<kOptLamb>(ch.flags[k], op, a0 + own[0], a1 + own[1]);
     __syncthreads();
     return s_r;  // written again only past another barrier
+}
+
+// The ratio of tensor k, of which pass A left rows, for one of the workgroups
+// of those rows: as pass A decided it; else the tensor's first workgroup
+// (`first`, dispatched ahead of its others) settles it once and publishes it in
+// the record after the last, which the others poll a bounded number of times
+// before they settle it themselves, in the same order.  (Such a tensor has more
+// than 2 * G units, so that record is within its workspace.)
+__device__ __forceinline__ float rest_ratio(const Chunk &ch, const OptParams &op, const LineWs &ws, uint32_t k, bool first,
+                                            uint32_t G, uint32_t tag) {
+    const unsigned long long w = ws.trust[ch.t0 + k];
+    if ((uint32_t)(w >> 32) == tag && (uint32_t)w != kFailed) return __uint_as_float((uint32_t)w);
+    unsigned long long *late = tensor_parts(ch, ws, k) + 4 * (uint64_t)G;
+    if (!first) {
+        __shared__ unsigned long long s_late;
+        if (threadIdx.x == 0) {
+            unsigned long long seen = 0;
+            for (uint32_t i = 0; i < op.trust_polls; i++) {
+                seen = __hip_atomic_load(late, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                if ((uint32_t)(seen >> 32) == tag) break;
+                __builtin_amdgcn_s_sleep(4);
+            }
+            s_late = seen;
+        }
+        __syncthreads();
+        if ((uint32_t)(s_late >> 32) == tag && op.trust_polls > 0) return __uint_as_float((uint32_t)s_late);
+    }
+    const float r = settled_ratio(ch, op, ws, k, G, tag);
+    if (first && threadIdx.x == 0)
+        __hip_atomic_store(late, ((unsigned long long)tag << 32) | __float_as_uint(r), __ATOMIC_RELAXED,
+                           __HIP_MEMORY_SCOPE_AGENT);
+    return r;
 }
 
 // What pass A left: the rows of units it does not hold (workgroups
@@ -1297,7 +1342,7 @@ __global__ __launch_bounds__(kWG) void lamb_b_kernel(const Chunk ch, const RestT
         }
         const uint64_t row = ch.base + ch.start[lo] + (uint64_t)(q - rt.begin[lo]) * kRow;
         const float lam = (ch.flags[lo] & 1u) ? op.wd : 0.0f;
-        const float lrr = op.lr * known_ratio(ch, op, ws, lo, tag);
+        const float lrr = op.lr * rest_ratio(ch, op, ws, lo, q + 1 == rt.begin[lo + 1], rt.grid_a, tag);
         redo_row(op, x, m, v, row, ch.base + ch.start[lo + 1], lam, lrr);
         return;
     }
@@ -1308,16 +1353,29 @@ __global__ __launch_bounds__(kWG) void lamb_b_kernel(const Chunk ch, const RestT
         if (threadIdx.x == 0) ws.epoch[0] = epoch + 1u;
     }
     if (*ws.gave_up != tag) return;
-    for (uint32_t k = 0; k < ch.nt; k++) {
+    // The held rows of the tensors given up, one after the other, in equal
+    // shares: a workgroup settles the ratios of the few tensors in its own.
+    __shared__ uint32_t s_rows[kChunkTensors];
+    for (uint32_t k = threadIdx.x; k < ch.nt; k += kWG) {
         const uint32_t units = ch.begin[k + 1] - ch.begin[k];
-        if (units == 0 || ws.trust[ch.t0 + k] != (((unsigned long long)tag << 32) | kFailed)) continue;
+        const bool gone = units > 0 && ws.trust[ch.t0 + k] == (((unsigned long long)tag << 32) | kFailed);
+        s_rows[k] = gone ? 2 * (units < op.hold ? units : op.hold) : 0;
+    }
+    __syncthreads();
+    uint64_t all = 0;
+    for (uint32_t k = 0; k < ch.nt; k++) all += s_rows[k];
+    const uint64_t lo = all * q / step, hi = all * (q + 1) / step;
+    uint64_t at = 0;  // rows of the tensors before k
+    for (uint32_t k = 0; k < ch.nt && at < hi; at += s_rows[k], k++) {
+        const uint64_t a = lo > at ? lo - at : 0, b = hi - at < s_rows[k] ? hi - at : s_rows[k];
+        if (a >= b) continue;
         const uint64_t t_hi = ch.base + ch.start[k + 1];
         const float lam = (ch.flags[k] & 1u) ? op.wd : 0.0f;
-        const float r_t = known_ratio(ch, op, ws, k, tag);
-        if (q == 0 && threadIdx.x == 0 && trust_out) trust_out[ch.t0 + k] = r_t;
-        const uint32_t first = units > op.hold ? 2 * (units - op.hold) : 0;  // the held rows: [first, 2 * units)
-        for (uint32_t i = first + q; i < 2 * units; i += step) {
-            const uint64_t row = ch.base + ch.start[k] + (uint64_t)i * kRow;
+        const float r_t = settled_ratio(ch, op, ws, k, rt.grid_a, tag);
+        if (a == 0 && threadIdx.x == 0 && trust_out) trust_out[ch.t0 + k] = r_t;
+        const uint32_t first = 2 * (ch.begin[k + 1] - ch.begin[k]) - s_rows[k];  // the first held row
+        for (uint64_t i = first + a; i < first + b; i++) {
+            const uint64_t row = ch.base + ch.start[k] + i * kRow;
             if (row < t_hi) redo_row(op, x, m, v, row, t_hi, lam, op.lr * r_t);
         }
     }

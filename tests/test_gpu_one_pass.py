@@ -93,6 +93,32 @@ def test_one_pass_step(table, src):
         D.dedloc_test_trust_polls(old)
 
 
+def test_one_pass_records():
+    """Tensors around the number of workgroups, each of which leaves one record
+    of its sums per tensor: one unit fewer and one more than there are
+    workgroups, as many (whole and with a last unit of one row), and around
+    twice as many, beyond which pass B has rows of its own and publishes the
+    ratio of a tensor given up."""
+    G = 3 * torch.cuda.get_device_properties(0).multi_processor_count
+    sizes = [(G - 1) * 4096 + 8, G * 4096 - 2048, G * 4096, G * 4096 + 8, 2 * G * 4096 - 4096, 2 * G * 4096 + 2056,
+             4 * G * 4096 + 8]
+    print(f"\n[one pass] records of {G} workgroups", flush=True)
+    off, flags, x, m, v, g, grad, scales = _inputs(sizes, "fp16")
+    flags[:] = 3
+    host = [t.cpu().numpy() for t in (x, m, v, g)]
+    want = oracle.lamb(*host, off, flags, oracle.lamb_cfg(**CFG))
+    old = D.dedloc_test_trust_polls(4096)
+    try:
+        got = _step((x, m, v), "fp16", off, flags, grad, scales)
+        _check(got, want, float(np.max(np.abs(host[0]))))
+        for polls in (0, 1, 4096):
+            D.dedloc_test_trust_polls(polls)
+            for a, b in zip(got, _step((x, m, v), "fp16", off, flags, grad, scales)):
+                assert torch.equal(a.view(torch.int32), b.view(torch.int32)), polls
+    finally:
+        D.dedloc_test_trust_polls(old)
+
+
 @pytest.mark.parametrize("table", ["edges", "ragged"])
 @pytest.mark.parametrize("n_peers,local", [(3, None), (9, 4), (66, None), (66, 65)])
 def test_one_pass_round(table, n_peers, local):

@@ -5,8 +5,10 @@ takes the best of several repeats of each, so that neither the machine's
 speed nor a passing disturbance decides; the bounds lie well between what the
 bytes give and the time of the mistake each one guards against."""
 
+import numpy as np
 import pytest
 
+from paper_2106_10207_amd import dedloc as D
 from paper_2106_10207_amd import harness as H
 from paper_2106_10207_amd import workloads as W
 
@@ -48,3 +50,32 @@ def test_local_gradient_in_the_round_beats_its_own_encode():
     fused, apart = _best_us([dr.call, separate])
     print(f"in the round {fused:.1f} us, encoded before it {apart:.1f} us", flush=True)
     assert fused <= apart
+
+
+def _step(sizes):
+    """A call of the LAMB step on an fp32 gradient, tensors of these sizes."""
+    off = np.concatenate([[0], np.cumsum(sizes)]).astype(np.uint64)
+    P = int(off[-1])
+    x = torch.randn(P, device=DEV).mul_(0.02)
+    m, v, g = torch.zeros(P, device=DEV), torch.full((P,), 1e-6, device=DEV), torch.randn(P, device=DEV).mul_(1e-3)
+    flags, cfg, ws = np.full(len(sizes), 3, np.uint8), D.lamb_cfg(step=10), D.make_workspace(P, off)
+    return lambda stream=None: D.dedloc_lamb_step(x, m, v, g, off, flags, cfg, ws=ws, stream=stream)
+
+
+@pytest.mark.parametrize("polls", [4096, 0])
+def test_one_large_tensor_takes_no_longer_than_its_bytes(polls):
+    """2^28 elements in one tensor: nearly all of its rows are updated by the
+    second pass, 40 bytes an element against 28 for the same elements in 64
+    tensors (measured 1.92 against 1.38 ms; given up by every workgroup that
+    waits, 1.96 to 2.05).  With a partial sum per 4096 elements and the ratio
+    formed again by every workgroup of the second pass it took 34 ms."""
+    print(f"\n[time] one large tensor, polls {polls}", flush=True)
+    one, split = _step([1 << 28]), _step([1 << 22] * 64)
+    (apart,) = _best_us([split], 3, 3)
+    old = D.dedloc_test_trust_polls(polls)
+    try:
+        (whole,) = _best_us([one], 3, 3)
+    finally:
+        D.dedloc_test_trust_polls(old)
+    print(f"one tensor {whole:.0f} us, 64 tensors {apart:.0f} us", flush=True)
+    assert whole <= 2.5 * apart
