@@ -443,11 +443,11 @@ const char *dedloc_kernel_name(int kind);
 
 /* Test hook of the LAMB and LARS steps and rounds.  One workgroup per tensor
  * forms the tensor's trust ratio and publishes it; the others poll for it at
- * most `polls` times (default 4096; at most 512 where LAMB holds the
- * parameters on chip meanwhile), then do without: they compute it
- * themselves, in the same order, or leave the tensor to the pass that
- * follows.  The results are the same bits for every value.  Process-wide,
- * read when a call is made; returns the previous value. */
+ * most `polls` times (default 4096; fewer where LAMB holds the parameters on
+ * chip meanwhile and other work keeps part of its grid from running), then
+ * do without: they compute it themselves, in the same order, or leave the
+ * tensor to the pass that follows.  The results are the same bits for every
+ * value.  Process-wide, read when a call is made; returns the previous value. */
 uint32_t dedloc_test_trust_polls(uint32_t polls);
 
 #ifdef __cplusplus

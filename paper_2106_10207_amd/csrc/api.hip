@@ -305,7 +305,7 @@ void make_plan(int opt, bool peers, uint64_t P, const uint64_t *off, const uint8
 // one workspace all advance the same one.
 LineWs carve_line(const Plan &pl, void *ws) {
     char *b = (char *)ws;
-    return {(uint32_t *)b, (uint32_t *)(b + 128), (unsigned long long *)(b + 256),
+    return {(uint32_t *)b, (unsigned long long *)(b + 128), (unsigned long long *)(b + 256),
             (unsigned long long *)(b + 256 + pl.ws_part)};
 }
 
@@ -413,14 +413,8 @@ int run_opt(int opt, int src_a, int src_b, const Plan &pl, const PeerTable *peer
     OptParams op = op_in;
     // One pass: a unit leaves the line kLineUnits turns after it entered, and
     // the last unit of its tensor must have been taken a turn before that.
-    // A wait is then one for the sums (a few us); if other work on the GPU
-    // keeps part of the grid from running, it ends after about half a
-    // millisecond, and pass B does the rest.
     const uint32_t cus = pl.one_pass ? cu_count() : 0, groups = cus * kLineGroups;
-    if (pl.one_pass) {
-        op.hold = (kLineUnits - 1) * groups;
-        op.trust_polls = std::min(op.trust_polls, 512u);
-    }
+    if (pl.one_pass) op.hold = (kLineUnits - 1) * groups;
     for (const Chunk &ch : pl.chunks) {
         hipError_t e;
         if (pl.one_pass) {

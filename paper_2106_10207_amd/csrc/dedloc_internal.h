@@ -41,6 +41,8 @@ constexpr int kLineLds = 3;
 constexpr int kLineUnits = (kLineRegs + kLineLds) / 2;  // units (two rows) in a line
 // peer loads in flight per lane there (4, 8, 16: ALBERT-large with 16 peers 188, 199, 213 us)
 constexpr int kLinePeerBatch = 4;
+constexpr uint32_t kLineLast = 8;        // workgroups that say that the whole grid runs
+constexpr uint32_t kLineShortWait = 48;  // polls of a wait while it does not
 constexpr int kMaxPeers = 64;          // peer table lives in the kernel arguments
 constexpr int kI8Block = 1024;         // int8 codec block = one wave64 x 16 codes
 constexpr int kI8PerLane = 16;
@@ -166,7 +168,9 @@ struct TileWs {
 // that wrote it.
 struct LineWs {
     uint32_t *epoch;             // [0]: read by pass A, advanced by pass B; [1]: pass A's value for pass B
-    uint32_t *gave_up;           // the tag if any tensor of the launch was given up
+    unsigned long long *state;   // low half: the tag if any tensor of the launch was given up;
+                                 // high half: how many of the grid's last kLineLast workgroups run
+                                 // (zeroed by pass B; other contents only shorten a launch's waits)
     unsigned long long *part;    // 16 bytes per row: records of partial sums
     unsigned long long *trust;   // per tensor: (tag << 32) | bits of r_t
 };

@@ -971,8 +971,20 @@ __device__ __forceinline__ bool get_part(const unsigned long long *w, uint32_t t
            (uint32_t)(q[3] >> 32) == tag;
 }
 
-__device__ __forceinline__ bool gave_up(const LineWs &ws, uint32_t tag) {
-    return __hip_atomic_load(ws.gave_up, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == tag;
+// Whether a wait ends with poll i.  Once every workgroup of the grid runs,
+// whatever is waited for comes, and waiting for the slower ones is where the
+// faster ones belong (up to 400 polls in a round of 64 peers, more on 500M
+// elements).  While other work on the GPU keeps some of them from starting, a
+// wait may be for them, so it ends after 48 polls (some 40 us) and the tensor is
+// left to pass B; after that no wait of the launch is longer than 16.
+// Workgroups are dispatched in order on each of the (at most 8) XCDs, so with
+// the grid's last 8 running all are.  (Two steps of 2^25 elements in one tensor
+// on two streams, each keeping part of the other's grid from starting: 541 us the
+// pair with a bound of 512 polls, 460 with this, 437 one after the other.)
+__device__ __forceinline__ bool stop_waiting(const LineWs &ws, uint32_t tag, uint32_t i) {
+    if (i % 16 != 15) return false;
+    const unsigned long long w = __hip_atomic_load(ws.state, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    return (uint32_t)w == tag || (i + 1 >= kLineShortWait && (uint32_t)(w >> 32) != kLineLast);
 }
 
 // The sums of a record once it is there, polling at most `polls` times, and less
@@ -981,7 +993,7 @@ __device__ __forceinline__ bool wait_part(const LineWs &ws, const unsigned long 
                                           double &a, double &b) {
     for (uint32_t i = 0; i < polls; i++) {
         if (get_part(w, tag, a, b)) return true;
-        if (i % 16 == 15 && gave_up(ws, tag)) break;
+        if (stop_waiting(ws, tag, i)) break;
         __builtin_amdgcn_s_sleep(4);
     }
     return false;
@@ -1064,17 +1076,22 @@ __device__ __forceinline__ uint32_t decide(unsigned long long *word, unsigned lo
     return (uint32_t)seen;
 }
 
-// Wait for the word's decision (`seen`: its content when last looked at).
-__device__ __forceinline__ uint32_t await_ratio(const LineWs &ws, const OptParams &op, unsigned long long *word,
-                                                unsigned long long seen, uint32_t tag) {
-    for (uint32_t i = 0; i < op.trust_polls && (uint32_t)(seen >> 32) != tag; i++) {
-        if (i % 16 == 15 && gave_up(ws, tag)) break;
+// Wait for the word's decision (`seen`: its content when last looked at).  A
+// lane that only follows another on the same word (`mine` false) decides nothing
+// and has no answer: a compare-and-swap by 64 lanes on one word takes 64 turns.
+__device__ __forceinline__ uint32_t await_ratio(const LineWs &ws, uint32_t polls, unsigned long long *word,
+                                                unsigned long long seen, uint32_t tag, bool mine) {
+    for (uint32_t i = 0; i < polls && (uint32_t)(seen >> 32) != tag; i++) {
+        if (stop_waiting(ws, tag, i)) break;
         __builtin_amdgcn_s_sleep(4);
         seen = __hip_atomic_load(word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
     if ((uint32_t)(seen >> 32) == tag) return (uint32_t)seen;
-    const uint32_t got = decide(word, seen, tag, kFailed);
-    if (got == kFailed) __hip_atomic_store(ws.gave_up, tag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    uint32_t got = kFailed;
+    if (mine) {
+        got = decide(word, seen, tag, kFailed);
+        if (got == kFailed) __hip_atomic_store((uint32_t *)ws.state, tag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
     return got;
 }
 
@@ -1098,6 +1115,11 @@ __global__ __launch_bounds__(kWG, kLineGroups) void lamb_a_kernel(const Chunk ch
     // the tag as pass B reads it (ws.epoch[0] is advanced there, and read
     // here only)
     if (blockIdx.x == 0 && threadIdx.x == 0) ws.epoch[1] = epoch;
+    // the grid's last workgroups say that they run (for a smaller grid's missing
+    // ones workgroup 0 does)
+    if (blockIdx.x + kLineLast >= G && threadIdx.x == 0)
+        __hip_atomic_fetch_add((uint32_t *)ws.state + 1, blockIdx.x == 0 ? kLineLast - G + 1 : 1u, __ATOMIC_RELAXED,
+                               __HIP_MEMORY_SCOPE_AGENT);
     float xr[NR][8], dr[NR][8];
     uint32_t slot = 0, it = 0;  // slot: (it - NR) % NL
     auto unpark = [&](uint32_t sl, float *xp, float *dp) {
@@ -1188,14 +1210,15 @@ __global__ __launch_bounds__(kWG, kLineGroups) void lamb_a_kernel(const Chunk ch
                     const uint32_t low = ok ? __float_as_uint(rt) : kFailed;
                     const unsigned long long seen = __hip_atomic_load(word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                     const uint32_t got = decide(word, seen, tag, low);
-                    if (got == kFailed) __hip_atomic_store(ws.gave_up, tag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    if (got == kFailed) __hip_atomic_store((uint32_t *)ws.state, tag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                     else if (trust_out) trust_out[ch.t0 + t.k] = rt;
                 }
             }
             s0 = s1 = 0.0;
         }
         if (leaves) {
-            const uint32_t low = __builtin_amdgcn_readfirstlane(await_ratio(ws, op, ws.trust + ch.t0 + to.k, q, tag));
+            const uint32_t low = __builtin_amdgcn_readfirstlane(
+                await_ratio(ws, op.trust_polls, ws.trust + ch.t0 + to.k, q, tag, (threadIdx.x & 63) == 0));
             if (low != kFailed) {
                 float xp[8], dp[8];
                 unpark(slot, xp, dp);
@@ -1236,7 +1259,8 @@ __global__ __launch_bounds__(kWG, kLineGroups) void lamb_a_kernel(const Chunk ch
         const UnitAt u(ch, blockIdx.x + (it - 1 - (threadIdx.x & 63)) / 2 * G, t.k);
         unsigned long long *word = ws.trust + ch.t0 + u.k;
         if (u.held(op))
-            r_lane = await_ratio(ws, op, word, __hip_atomic_load(word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT), tag);
+            r_lane = await_ratio(ws, op.trust_polls, word, __hip_atomic_load(word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT), tag,
+                                 true);
     }
     for (uint32_t i = left; i > 0; i--) {
         const UnitAt u(ch, blockIdx.x + (it - i) / 2 * G, t.k);
@@ -1325,7 +1349,7 @@ __device__ __forceinline__ float rest_ratio(const Chunk &ch, const OptParams &op
 // What pass A left: the rows of units it does not hold (workgroups
 // [0, n_rest), last to first: the re-reads start with what pass A touched
 // last), and all held rows of tensors that were given up, if there are any.
-// Also r = 1 of empty tensors, and the next launch's tag.
+// Also r = 1 of empty tensors, and the next launch's tag and state.
 __global__ __launch_bounds__(kWG) void lamb_b_kernel(const Chunk ch, const RestTable rt, const OptParams op,
                                                      float *__restrict__ x, float *__restrict__ m,
                                                      float *__restrict__ v, LineWs ws, uint32_t nonce,
@@ -1350,9 +1374,12 @@ __global__ __launch_bounds__(kWG) void lamb_b_kernel(const Chunk ch, const RestT
     if (q == 0) {
         for (uint32_t k = threadIdx.x; k < ch.nt; k += kWG)
             if (trust_out && ch.begin[k] == ch.begin[k + 1]) trust_out[ch.t0 + k] = 1.0f;
-        if (threadIdx.x == 0) ws.epoch[0] = epoch + 1u;
+        if (threadIdx.x == 0) {
+            ws.epoch[0] = epoch + 1u;
+            ((uint32_t *)ws.state)[1] = 0u;
+        }
     }
-    if (*ws.gave_up != tag) return;
+    if (*(const uint32_t *)ws.state != tag) return;
     // The held rows of the tensors given up, one after the other, in equal
     // shares: a workgroup settles the ratios of the few tensors in its own.
     __shared__ uint32_t s_rows[kChunkTensors];

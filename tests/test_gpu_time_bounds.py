@@ -79,3 +79,31 @@ def test_one_large_tensor_takes_no_longer_than_its_bytes(polls):
         D.dedloc_test_trust_polls(old)
     print(f"one tensor {whole:.0f} us, 64 tensors {apart:.0f} us", flush=True)
     assert whole <= 2.5 * apart
+
+
+def test_two_streams_take_little_longer_than_one():
+    """Two one-pass steps, each in the other's way on a stream of its own: a
+    workgroup whose tensor waits for workgroups that cannot start gives up
+    soon, and the second pass does what is left.  Measured for the pair, two
+    streams against one: 463 / 439 us; with waits of 512 polls and a ratio
+    formed by every workgroup of the second pass 1255 / 447."""
+    print("\n[time] two streams", flush=True)
+    steps = [_step([1 << 25]) for _ in range(2)]
+    streams = [torch.cuda.Stream() for _ in range(2)]
+
+    def apart():
+        for f, s in zip(steps, streams):
+            s.wait_stream(torch.cuda.current_stream())
+            for _ in range(4):
+                f(s)
+        for s in streams:
+            torch.cuda.current_stream().wait_stream(s)
+
+    def together():
+        for _ in range(4):
+            for f in steps:
+                f()
+
+    two, one = _best_us([apart, together], 5, 3)
+    print(f"two streams {two:.0f} us, one {one:.0f} us", flush=True)
+    assert two <= 1.7 * one
