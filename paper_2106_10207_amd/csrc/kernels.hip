@@ -1374,7 +1374,8 @@ __global__ __launch_bounds__(kWG) void lamb_b_kernel(const Chunk ch, const RestT
     if (q == 0) {
         for (uint32_t k = threadIdx.x; k < ch.nt; k += kWG)
             if (trust_out && ch.begin[k] == ch.begin[k + 1]) trust_out[ch.t0 + k] = 1.0f;
-        if (threadIdx.x == 0) {
+        // (a chunk of empty tensors has no pass A, which alone sets epoch[1])
+        if (threadIdx.x == 0 && ch.begin[ch.nt] > 0) {
             ws.epoch[0] = epoch + 1u;
             ((uint32_t *)ws.state)[1] = 0u;
         }

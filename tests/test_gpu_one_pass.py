@@ -171,3 +171,22 @@ def test_two_steps_at_once():
     for got in sets:
         for a, b in zip(got[:4], want):
             assert torch.equal(a.view(torch.int32), b.view(torch.int32))
+
+
+def test_chunk_of_empty_tensors_leaves_the_counter():
+    """192 empty tensors, a launch chunk of their own, ahead of a table that
+    takes the pass: the workspace's counter, its first word, which two-pass calls
+    advance alone, only ever goes forward."""
+    print("\n[one pass] empty chunk", flush=True)
+    off, flags, x, m, v, g, _, _ = _inputs([0] * 192 + [SMALLEST], "f32")
+    host = [t.cpu().numpy() for t in (x, m, v, g)]
+    want = oracle.lamb(*host, off, flags, oracle.lamb_cfg(**CFG))
+    ws = D.make_workspace(x.numel(), off)
+    words = ws.view(torch.int32)
+    words[0], words[1] = 1000, 5  # 1000 calls so far, the sixth of them this pass
+    for n in (1001, 1002):
+        got = _step((x, m, v), "f32", off, flags, g, None, ws)
+        torch.cuda.synchronize()
+        assert int(words[0]) == n
+        _check(got, want, float(np.max(np.abs(host[0]))))
+        assert torch.all(got[3][:192] == 1.0)
