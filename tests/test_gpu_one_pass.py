@@ -190,3 +190,98 @@ def test_chunk_of_empty_tensors_leaves_the_counter():
         assert int(words[0]) == n
         _check(got, want, float(np.max(np.abs(host[0]))))
         assert torch.all(got[3][:192] == 1.0)
+
+
+def test_one_pass_in_a_graph_as_consecutive_steps():
+    """Replays of a captured step as consecutive steps: the state evolves, so
+    every replay has other ratios and other sums, under a tag that only the
+    workspace's counter makes its own.  Bit for bit the eager steps."""
+    print("\n[one pass] graph", flush=True)
+    off, flags, x, m, v, g, _, _ = _inputs([SMALLEST, 4096 * 5 + 8, 1 << 20], "f32")
+    flags[:] = 3
+    ws = D.make_workspace(x.numel(), off)
+    tr = torch.full((len(flags),), -1.0, device=DEV)
+    state = [t.clone() for t in (x, m, v)]
+    cfg = D.lamb_cfg(**CFG)
+
+    def step(stream=None):
+        D.dedloc_lamb_step(*state, g, off, flags, cfg, trust_out=tr, ws=ws, stream=stream)
+
+    def outs():
+        torch.cuda.synchronize()
+        return [t.clone().view(torch.int32) for t in (*state, tr)]
+
+    def reset():
+        for t, t0 in zip(state, (x, m, v)):
+            t.copy_(t0)
+        torch.cuda.synchronize()
+
+    want = []
+    for _ in range(4):
+        step()
+        want.append(outs())
+    assert not torch.equal(want[0][3], want[1][3])  # the ratios change from step to step
+    reset()
+    graph, s = torch.cuda.CUDAGraph(), torch.cuda.Stream()
+    with torch.cuda.graph(graph, stream=s):
+        step(s)
+    reset()
+    for n in range(4):
+        graph.replay()
+        for a, b in zip(outs(), want[n]):
+            assert torch.equal(a, b), n
+        _ = torch.ones(1024, device=DEV).sum().item()  # eager work between replays
+
+
+def test_two_tables_in_turn_on_one_workspace():
+    """A one-pass and a two-pass table, and a one-pass table whose records lie
+    elsewhere, take turns on one workspace."""
+    print("\n[one pass] one workspace", flush=True)
+    cases = [_inputs(sizes, "f32", seed) for seed, sizes in
+             ((5, [SMALLEST, 2048 * 3]), (6, [4096 * 3, 8, 2056]), (7, [2051 * 8, SMALLEST + 8]))]
+    want = [_step(c[2:5], "f32", c[0], c[1], c[5], None) for c in cases]
+    ws = D.make_workspace(cases[2][2].numel(), cases[2][0])
+    ws.random_()
+    for _ in range(2):
+        for c, w in zip(cases, want):
+            for a, b in zip(_step(c[2:5], "f32", c[0], c[1], c[5], None, ws), w):
+                assert torch.equal(a.view(torch.int32), b.view(torch.int32))
+
+
+@pytest.mark.parametrize("cfg", [dict(CFG, force_unit_trust=True), dict(CFG, bias_correction=False), dict(CFG, eps=0.0)],
+                         ids=["unit trust", "no bias correction", "eps 0"])
+def test_one_pass_options(cfg):
+    print(f"\n[one pass] {cfg}", flush=True)
+    off, flags, x, m, v, g, _, _ = _inputs([SMALLEST, 4096 + 8, 3 * 4096 + 1], "f32")
+    host = [t.cpu().numpy() for t in (x, m, v, g)]
+    want = oracle.lamb(*host, off, flags, oracle.lamb_cfg(**cfg))
+    tr = torch.full((len(flags),), -1.0, device=DEV)
+    D.dedloc_lamb_step(x, m, v, g, off, flags, D.lamb_cfg(**cfg), trust_out=tr)
+    torch.cuda.synchronize()
+    _check((x, m, v, tr), want, float(np.max(np.abs(host[0]))))
+
+
+def test_one_pass_non_finite_gradients():
+    """An infinity in one tensor (its norm, so r = 0 there), a NaN in another (r =
+    1) and in a tensor's last row: NaN by position, all else as the oracle has
+    it, and the same bits when every tensor is given up."""
+    print("\n[one pass] non-finite", flush=True)
+    off, flags, x, m, v, g, _, _ = _inputs([SMALLEST, 5 * 4096, 6 * 4096 + 8, 4096], "f32")
+    flags[:] = 3
+    g[int(off[1]) + 77] = float("inf")
+    g[int(off[2]) + 4099] = float("nan")
+    g[int(off[4]) - 1] = float("nan")
+    host = [t.cpu().numpy() for t in (x, m, v, g)]
+    want = oracle.lamb(*host, off, flags, oracle.lamb_cfg(**CFG))
+    got = _step((x, m, v), "f32", off, flags, g, None)
+    for a, b in zip(got, want):
+        a = a.cpu().numpy()
+        assert np.array_equal(np.isnan(a), np.isnan(b)) and np.array_equal(np.isinf(a), np.isinf(b))
+        fine = np.isfinite(b)
+        assert float(np.max(np.abs(a[fine].astype(np.float64) - b[fine]))) <= 1e-5 * float(np.max(np.abs(b[fine])))
+    old = D.dedloc_test_trust_polls(0)
+    try:
+        for a, b in zip(got, _step((x, m, v), "f32", off, flags, g, None)):
+            assert torch.equal(a.view(torch.int32), b.view(torch.int32))
+    finally:
+        D.dedloc_test_trust_polls(old)
