@@ -170,11 +170,17 @@ def _check(rc: int):
         raise DedlocError(rc, load().dedloc_last_error().decode())
 
 
+_addressof, _from_buffer = ctypes.addressof, ctypes.c_char.from_buffer
+
+
 def _ptr(t) -> Optional[int]:
     if t is None:
         return None
     if isinstance(t, np.ndarray):
-        return t.__array_interface__["data"][0]  # the same address as t.ctypes.data, at a third of its time
+        try:
+            return _addressof(_from_buffer(t))  # the same address as t.ctypes.data, at a quarter of its time
+        except (TypeError, ValueError):  # read-only, empty or not contiguous
+            return t.ctypes.data
     return t.data_ptr()
 
 
@@ -408,7 +414,6 @@ class RoundCall:
         self.args = None
         self.codec, self.block = codec, block
         self.lars = isinstance(cfg, dedloc_lars_cfg)
-        self._tables = None
         self.out = (_dev(out_codes, _code_bytes(codec, P), "out_codes"),
                     _dev(out_scales, _scale_bytes(codec, P, block), "out_scales"), _dev(x, 4 * P, "x", f32=True),
                     None if self.lars else _dev(m, 4 * P, "m", f32=True), _dev(v, 4 * P, "v", f32=True), P,
@@ -418,11 +423,8 @@ class RoundCall:
 
     def __call__(self, stream=None):
         oc, osc, x, m, v, P, tr, om, ws, wsb = self.out
-        t = self._tables  # the host tables and their addresses, looked up again if one was replaced
-        if t is None or t[0] is not self.cnt or t[1] is not self.bnd or t[2] is not self.off or t[3] is not self.fl:
-            t = (self.cnt, self.bnd, self.off, self.fl)
-            self._tables = t = t + tuple(_ptr(a) for a in t)
-        cnt, bnd, off, fl = t[4:]
+        # looked up on every call: a table can be replaced, or resized in place
+        cnt, bnd, off, fl = _ptr(self.cnt), _ptr(self.bnd), _ptr(self.off), _ptr(self.fl)
         cfg = ctypes.byref(self.cfg)
         lib = load()
         if self.lars:

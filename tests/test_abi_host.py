@@ -301,3 +301,55 @@ def test_codec_and_weights_validation():
     assert lib.dedloc_weights(c.ctypes.data, 0, w.ctypes.data) == D.DEDLOC_ERR_INVALID_ARG
     big = np.array([1 << 24, 1], np.uint32)
     assert lib.dedloc_weights(big.ctypes.data, 2, w.ctypes.data) == D.DEDLOC_ERR_INVALID_ARG
+
+
+class _FakeTensor:
+    """As much of a device tensor as the binding's marshalling looks at."""
+
+    def __init__(self, n, itemsize, dtype=None):
+        self.n, self.itemsize, self.dtype, self.is_cuda, self.nbytes = n, itemsize, dtype, True, n * itemsize
+
+    def is_contiguous(self):
+        return True
+
+    def numel(self):
+        return self.n
+
+    def element_size(self):
+        return self.itemsize
+
+    def data_ptr(self):
+        return 4096
+
+
+def test_round_call_follows_tables_resized_in_place(monkeypatch):
+    """A RoundCall passes the addresses its host tables have at the call: one
+    replaced, rewritten or resized in place (same object, other memory) since
+    the last call included."""
+    torch = pytest.importorskip("torch")
+    seen = []
+
+    class Lib:
+        def dedloc_round(self, pc, ps, cnt, n, bnd, *rest):
+            seen.append((list((ctypes.c_uint32 * n).from_address(cnt)), bnd))
+            return D.DEDLOC_OK
+
+    monkeypatch.setattr(D, "load", lambda: Lib())
+    monkeypatch.setattr(D, "_stream", lambda stream=None: 0)
+    f32, i16 = _FakeTensor(64, 4, torch.float32), _FakeTensor(64, 2)
+    counts = np.array([3, 4], np.uint32)
+    call = D.RoundCall([i16, i16], counts, np.array([0, 64], np.uint64), D.DEDLOC_CODEC_FP16, i16, f32, f32, f32,
+                       np.array([0, 64], np.uint64), np.array([3], np.uint8), D.lamb_cfg(), _FakeTensor(4096, 1))
+    call()
+    counts[0] = 5
+    call()
+    assert seen[0][0] == [3, 4] and seen[1][0] == [5, 4]
+    call.cnt = np.array([7, 8], np.uint32)
+    call()
+    assert seen[2][0] == [7, 8]
+    bnd = np.zeros(4, np.uint64)
+    call.bnd = bnd
+    call()
+    bnd.resize(1 << 18, refcheck=False)  # moves
+    call()
+    assert seen[4][1] == bnd.ctypes.data and seen[4][1] != seen[3][1]
