@@ -251,7 +251,7 @@ def _stream(stream=None) -> Optional[int]:
 
 
 def _host(a, dtype) -> np.ndarray:
-    if type(a) is np.ndarray and a.dtype == dtype and a.flags.c_contiguous:
+    if type(a) is np.ndarray and a.ndim and a.dtype == dtype and a.flags.c_contiguous:
         return a
     return np.ascontiguousarray(np.asarray(a, dtype=dtype))
 

@@ -303,6 +303,13 @@ def test_codec_and_weights_validation():
     assert lib.dedloc_weights(big.ctypes.data, 2, w.ctypes.data) == D.DEDLOC_ERR_INVALID_ARG
 
 
+def test_scalar_array_is_a_table_of_one():
+    """A 0-d array of the table's own type passes as one entry, as a number of
+    any other type does."""
+    assert D.dedloc_weights(np.array(5, np.uint32)).tolist() == D.dedloc_weights(np.array(5)).tolist() == [1.0]
+    assert D.dedloc_partition(64, 1, np.array(3, np.uint64)).tolist() == [0, 64]
+
+
 class _FakeTensor:
     """As much of a device tensor as the binding's marshalling looks at."""
 
