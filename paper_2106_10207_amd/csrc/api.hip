@@ -203,6 +203,19 @@ LocalArgs local_in(const LocalArgs &la, uint32_t a, uint32_t b) {
     return r;
 }
 
+// Compute units of the current device (256 if it cannot be asked).
+uint32_t cu_count() {
+    static std::atomic<int> known[64];
+    int dev = 0, n = 0;
+    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return 256;
+    n = known[dev].load(std::memory_order_relaxed);
+    if (n == 0) {
+        if (hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n <= 0) n = 256;
+        known[dev].store(n, std::memory_order_relaxed);
+    }
+    return (uint32_t)n;
+}
+
 // Reduce peers [lo, hi) of the list in launches of kMaxPeers, chained through
 // `mean`; the launch holding peer hi - 1 encodes into out / out_scales when
 // `encode` is set.  Peers before lo must already be summed into `mean`.
@@ -215,7 +228,7 @@ int run_reduce(int32_t codec, const PeerList &pl, uint32_t lo, uint32_t hi, bool
         const ChainArgs ca = {a > 0 ? mean : nullptr, mean, encode && b == hi, local_in(la, a, b), 1, 0, 0};
         const hipError_t e = codec == DEDLOC_CODEC_FP16
                                  ? timed(K_REDUCE_FP16, s, [&] { return launch_reduce_fp16(gt, len, ca, s); })
-                                 : timed(K_REDUCE_I8, s, [&] { return launch_reduce_i8(gt, len, ca, s); });
+                                 : timed(K_REDUCE_I8, s, [&] { return launch_reduce_i8(gt, len, ca, cu_count(), s); });
         if (e != hipSuccess) return hip_fail(e, "reduce launch");
     }
     return DEDLOC_OK;
@@ -385,19 +398,6 @@ uint32_t next_nonce() {
     static std::atomic<uint32_t> ctr{(uint32_t)std::chrono::steady_clock::now().time_since_epoch().count() * 2654435761u ^
                                      (uint32_t)getpid()};
     return ctr.fetch_add(0x9E3779B9u, std::memory_order_relaxed);
-}
-
-// Compute units of the current device (the persistent grid's size).
-uint32_t cu_count() {
-    static std::atomic<int> known[64];
-    int dev = 0, n = 0;
-    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return 256;
-    n = known[dev].load(std::memory_order_relaxed);
-    if (n == 0) {
-        if (hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n <= 0) n = 256;
-        known[dev].store(n, std::memory_order_relaxed);
-    }
-    return (uint32_t)n;
 }
 
 // Per chunk of tensors: pass A (gradient from src_a) and pass B (LARS reads
@@ -877,7 +877,7 @@ int dedloc_group_allreduce(const void *const *peer_codes, const float *const *pe
             const ChainArgs ca = {nullptr, nullptr, 1, {-1, nullptr, nullptr, nullptr}, copies, gp.code_stride, gp.scale_stride};
             hipError_t e = codec == DEDLOC_CODEC_FP16
                                ? timed(K_REDUCE_FP16, s, [&] { return launch_reduce_fp16(gt, len, ca, s); })
-                               : timed(K_REDUCE_I8, s, [&] { return launch_reduce_i8(gt, len, ca, s); });
+                               : timed(K_REDUCE_I8, s, [&] { return launch_reduce_i8(gt, len, ca, cu_count(), s); });
             if (e != hipSuccess) return hip_fail(e, "group reduce launch");
         }
         memset(&gt, 0, sizeof gt);

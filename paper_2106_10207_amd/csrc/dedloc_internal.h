@@ -182,7 +182,8 @@ hipError_t launch_encode_i8(const float *x, uint64_t n, int8_t *codes, float *sc
 hipError_t launch_decode_i8(const int8_t *codes, const float *scales, uint64_t n, float *out,
                             hipStream_t s);
 hipError_t launch_reduce_fp16(const GroupTable &gt, uint64_t len, const ChainArgs &ca, hipStream_t s);
-hipError_t launch_reduce_i8(const GroupTable &gt, uint64_t len, const ChainArgs &ca, hipStream_t s);
+// cus: compute units of the device
+hipError_t launch_reduce_i8(const GroupTable &gt, uint64_t len, const ChainArgs &ca, uint32_t cus, hipStream_t s);
 hipError_t launch_lamb_a(int src, const Chunk &ch, uint32_t n_groups, const PeerTable &pt, const GradArgs &ga,
                          const OptParams &op, float *x, float *m, float *v, const LineWs &ws, uint32_t nonce,
                          float *trust_out, hipStream_t s);

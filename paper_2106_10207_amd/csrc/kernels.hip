@@ -1556,15 +1556,15 @@ hipError_t launch_reduce_fp16(const GroupTable &gt, uint64_t len, const ChainArg
     DEDLOC_LAUNCH(grid, reduce_fp16_kernel<kPeerBatch>, s, gt, len, ca);
 }
 
-hipError_t launch_reduce_i8(const GroupTable &gt, uint64_t len, const ChainArgs &ca, hipStream_t s) {
+hipError_t launch_reduce_i8(const GroupTable &gt, uint64_t len, const ChainArgs &ca, uint32_t cus, hipStream_t s) {
     const dim3 grid(grid_for(len, (uint64_t)kI8Block * (kWG / 64)), gt.n_groups);
-    // Few waves (under 16 a CU) and many peers: the serial chain of batches is
-    // what the launch takes, so the loads go out 16 at a time (30 peers: 1M
-    // elements 31.9 us a round against 37.0, 3M 48.7 / 50.7; 6M the other way
-    // round 77.7 / 73.1).  Also where batches of 4, of which 32 waves a CU run at
-    // once, leave a second generation nearly empty (10.5M elements 120.7 us
-    // against 125.7; 13M 169.3 / 168.0, 8M 88.8 / 84.1).
-    const uint64_t groups = (uint64_t)grid.x * grid.y, at_once = 256 * 8;
+    // Few waves (under 16 a CU, 4 workgroups) and many peers: the serial chain of
+    // batches is what the launch takes, so the loads go out 16 at a time (30 peers
+    // on 256 CUs: 1M elements 31.9 us a round against 37.0, 3M 48.7 / 50.7; 6M the
+    // other way round 77.7 / 73.1).  Also where batches of 4, of which 8 workgroups
+    // a CU run at once, leave a second generation nearly empty (10.5M elements
+    // 120.7 us against 125.7; 13M 169.3 / 168.0, 8M 88.8 / 84.1).
+    const uint64_t groups = (uint64_t)grid.x * grid.y, at_once = 8ull * cus;
     if (largest_group(gt) > 12 && (groups < at_once / 2 || (groups > at_once && groups <= at_once * 3 / 2)))
         DEDLOC_LAUNCH(grid, reduce_i8_kernel<kI8FewWaves>, s, gt, len, ca);
     DEDLOC_LAUNCH(grid, reduce_i8_kernel<kI8Batch>, s, gt, len, ca);
