@@ -848,8 +848,9 @@ __global__ __launch_bounds__(kWG) void opt_b_kernel(const Chunk ch, const GradAr
 
 // ------------------------------------------------------ LAMB in one pass
 
-// LAMB's rows without gaps in a wave's accesses (GF: row_at's layout).  The fused average keeps eight consecutive elements per lane, which its
-// 16-byte message accesses need.
+// A row of LAMB's one pass, without gaps in a wave's accesses (GF: row_at's
+// layout).  The fused average keeps eight consecutive elements per lane, which
+// its 16-byte message accesses need.
 template <bool GF>
 struct Row {
     uint64_t row, t_hi;
@@ -861,13 +862,15 @@ struct Row {
         return GF ? row + row_at(j >> 2) + (j & 3) < t_hi : e0() + j < t_hi;
     }
     // the lane's eight elements (zero past the end)
+    template <bool NT = true>
     __device__ __forceinline__ void load(const float *__restrict__ p, float *o) const {
         if (!GF) {
-            load8<true>(p, e0(), count8(e0(), t_hi), o);
+            load8<NT>(p, e0(), count8(e0(), t_hi), o);
         } else if (full()) {
 #pragma unroll
             for (int h = 0; h < 2; h++) {
-                const f32x4 a = __builtin_nontemporal_load((const f32x4 *)(p + row + row_at(h)));
+                const f32x4 *q = (const f32x4 *)(p + row + row_at(h));
+                const f32x4 a = NT ? __builtin_nontemporal_load(q) : *q;
 #pragma unroll
                 for (int j = 0; j < 4; j++) o[4 * h + j] = a[j];
             }
@@ -1143,7 +1146,13 @@ __global__ __launch_bounds__(kWG, kLineGroups) void lamb_a_kernel(const Chunk ch
     RawGrad<SRC> fg;
     auto fetch = [&](const Row<GF> &r) {
         if (r.row >= r.t_hi) return;
-        r.load(x, fx);
+        // x plain, m and v and all stores non-temporal: a cache that still holds
+        // part of x from the last call serves it (the same buffers again / three
+        // sets in turn: ALBERT-large's round 204.8 -> 201.7 / 204 -> 205 us, 40M
+        // elements 380 -> 370 / 400 -> 390, the step on 60M 360 -> 352 / 360 -> 352).
+        // With more of them plain the same buffers again gain more and others lose
+        // more: all loads 186 / 221, all 184 / 224, m's loads and stores 193 / 215.
+        r.template load<false>(x, fx);
         r.load(m, fm);
         r.load(v, fv);
         if constexpr (!kPeers) fg.load(ga, r);
