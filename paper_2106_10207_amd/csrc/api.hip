@@ -268,16 +268,36 @@ int check_tensors(uint64_t P, const uint64_t *off, uint32_t T) {
 constexpr uint64_t kOnePassElements = 1ull << 23;       // a message or fp32 gradient
 constexpr uint64_t kOnePassElementsPeers = 1ull << 24;  // the fused average
 constexpr uint64_t kOnePassPerTensor = 1ull << 18;
+// Of a tensor the grid's line holds its last 2 * 768 units on 256 CUs, 6.3M
+// elements; the rest takes a second pass all the same, and the fused average is
+// then slower in the persistent grid than in two plain passes.  So it takes the
+// one pass where the line holds a third of the elements.  One pass against two,
+// on the same buffers, 2, 8, 16 and 60 peers, us: tensors of 12M elements (held
+// 52%) 457 / 475, 574 / 596, 739 / 780, 1078 / 1075; 16.8M (37%) 394 / 397, 493 /
+// 498, 627 / 659, 1021 / 1009; 33M (19%) 277 / 268, 346 / 338, 430 / 441, 1028 /
+// 1010.  A message or fp32 gradient gains throughout (one tensor of 33M 223 / 235,
+// of 2^30 7.8 / 8.2 ms).
 // LARS: x and v of 2^24 elements are 128 MB, half of the Infinity Cache.
 // Non-temporal accesses beyond: 8.5M and 9M elements 61.6 / 65.0 and 75.2 / 78.0
 // us, 12M equal, 18M 148.6 / 141.8, 26M 201.5 / 198.1, 40M 232.5 / 222.5
 // (without / with).
 constexpr uint64_t kNtElements = 1ull << 24;
 
+// Units of a tensor that a persistent grid on this many CUs holds: a unit leaves
+// the line kLineUnits turns after it entered, and the last unit of its tensor
+// must have been taken a turn before that.
+uint32_t held_units(uint32_t cus) { return (kLineUnits - 1) * cus * kLineGroups; }
+
 void make_plan(int opt, bool peers, uint64_t P, const uint64_t *off, const uint8_t *flags, uint32_t T, Plan &pl) {
     uint64_t full = 0;  // tensors with elements
     for (uint32_t t = 0; t < T; t++) full += off[t + 1] > off[t];
     pl.one_pass = opt == kOptLamb && P >= (peers ? kOnePassElementsPeers : kOnePassElements) && P / full >= kOnePassPerTensor;
+    if (pl.one_pass && peers) {
+        const uint64_t line = (uint64_t)held_units(cu_count()) * 2 * kRow;
+        uint64_t held = 0;
+        for (uint32_t t = 0; t < T; t++) held += std::min(off[t + 1] - off[t], line);
+        pl.one_pass = 3 * held >= P;
+    }
     pl.nt = P >= kNtElements;
     const uint32_t per = pl.one_pass ? 2 : 1;  // rows per work item
     pl.chunks.clear();
@@ -411,10 +431,8 @@ int run_opt(int opt, int src_a, int src_b, const Plan &pl, const PeerTable *peer
     const int k_b = opt == kOptLamb ? K_LAMB_B : K_LARS_B;
     const uint32_t nonce = next_nonce();
     OptParams op = op_in;
-    // One pass: a unit leaves the line kLineUnits turns after it entered, and
-    // the last unit of its tensor must have been taken a turn before that.
     const uint32_t cus = pl.one_pass ? cu_count() : 0, groups = cus * kLineGroups;
-    if (pl.one_pass) op.hold = (kLineUnits - 1) * groups;
+    op.hold = held_units(cus);
     for (const Chunk &ch : pl.chunks) {
         hipError_t e;
         if (pl.one_pass) {
