@@ -68,8 +68,10 @@ def _parse():
 KERNEL_KINDS = {
     "dedloc::encode_fp16_kernel": "encode_fp16",
     "dedloc::encode_i8_kernel": "encode_i8",
-    "dedloc::decode_fp16_kernel": "decode_fp16",
-    "dedloc::decode_i8_kernel": "decode_i8",
+    "void dedloc::decode_fp16_kernel<false>": "decode_fp16",
+    "void dedloc::decode_fp16_kernel<true>": "decode_fp16",
+    "void dedloc::decode_i8_kernel<false>": "decode_i8",
+    "void dedloc::decode_i8_kernel<true>": "decode_i8",
     "void dedloc::reduce_fp16_kernel<4>": "reduce_fp16",
     "void dedloc::reduce_fp16_kernel<16>": "reduce_fp16",
     "void dedloc::reduce_i8_kernel<4>": "reduce_i8",

@@ -157,8 +157,9 @@ __global__ __launch_bounds__(kWG) void encode_fp16_kernel(const float *__restric
 #pragma unroll
         for (int h = 0; h < 2; h++) {
             const f32x4 a = ld_stream((const f32x4 *)(x + row + row_at(h)));
-            // plain stores: the message is read next (decoded at once, 17.7M
-            // elements 37.1 -> 33.3 us, 60M 116.8 -> 106.4)
+            // plain stores (non-temporal / plain): with the message read next, here
+            // decoded, 8M elements 18.7 / 13.2 us, 17.7M 37.1 / 33.8, 60M 116.8 / 106.4;
+            // alone 6.9 / 7.4, 15.6 / 17.8, 100M 90.4 / 86.3
             *(u32x2 *)(codes + row + row_at(h)) = u32x2{f2h(a[0]) | (f2h(a[1]) << 16), f2h(a[2]) | (f2h(a[3]) << 16)};
         }
     } else {
@@ -166,8 +167,23 @@ __global__ __launch_bounds__(kWG) void encode_fp16_kernel(const float *__restric
     }
 }
 
-// Non-temporal stores: the output is twice the message, and both it and the
-// decoded int8 vector ran 4 to 8% faster with them (17.7M to 60M elements).
+// NT: non-temporal stores of the decoded vector, from these sizes on.  A small
+// vector is found in the L2s by whoever reads it next (int8 decode, then accumulate,
+// plain / non-temporal: 65k elements 3.96 / 4.06 us, 262k 4.28 / 4.46, 1M 6.42 / 6.66,
+// 1.5M 8.00 / 8.18, 2M 9.40 / 9.25; fp16 1M 4.85 / 4.87, 1.5M 5.57 / 5.51, 2M 6.63 /
+// 6.31); a large one leaves them room for the message and the reader's other data
+// (8M int8: alone 7.70 / 5.94, after the encode 16.5 / 12.9, before an accumulate 22.6 /
+// 22.5; 17.7M fp16: 17.1 / 16.7, 37.1 / 33.8, 48.6 / 49.1).  A reader that writes as much
+// again into a third buffer loses by it where the Infinity Cache would have held the
+// vector (40M fp16: 82.8 / 94.1).
+constexpr uint64_t kNtDecodeFp16 = 1ull << 20, kNtDecodeI8 = 1ull << 21;
+template <bool NT>
+__device__ __forceinline__ void st_decoded(f32x4 *p, f32x4 v) {
+    if (NT) __builtin_nontemporal_store(v, p);
+    else *p = v;
+}
+
+template <bool NT>
 __global__ __launch_bounds__(kWG) void decode_fp16_kernel(const uint16_t *__restrict__ codes, uint64_t n,
                                                           float *__restrict__ out) {
     const uint64_t row = (uint64_t)blockIdx.x * kRow;
@@ -175,8 +191,8 @@ __global__ __launch_bounds__(kWG) void decode_fp16_kernel(const uint16_t *__rest
 #pragma unroll
         for (int h = 0; h < 2; h++) {
             const u32x2 c = *(const u32x2 *)(codes + row + row_at(h));
-            __builtin_nontemporal_store(f32x4{h2f(c[0] & 0xffffu), h2f(c[0] >> 16), h2f(c[1] & 0xffffu), h2f(c[1] >> 16)},
-                                        (f32x4 *)(out + row + row_at(h)));
+            st_decoded<NT>((f32x4 *)(out + row + row_at(h)),
+                       f32x4{h2f(c[0] & 0xffffu), h2f(c[0] >> 16), h2f(c[1] & 0xffffu), h2f(c[1] >> 16)});
         }
     } else {
         for (uint64_t e = row + threadIdx.x; e < n; e += kWG) out[e] = h2f(codes[e]);
@@ -246,6 +262,7 @@ __global__ __launch_bounds__(kWG) void encode_i8_kernel(const float *__restrict_
     store_i8_lane(codes, scales, n, blk, c, s);
 }
 
+template <bool NT>
 __global__ __launch_bounds__(kWG) void decode_i8_kernel(const int8_t *__restrict__ codes,
                                                         const float *__restrict__ scales, uint64_t n,
                                                         float *__restrict__ out) {
@@ -257,8 +274,8 @@ __global__ __launch_bounds__(kWG) void decode_i8_kernel(const int8_t *__restrict
 #pragma unroll
         for (int q = 0; q < 4; q++) {
             const unsigned c = *(const unsigned *)(codes + I8_ELEM(b0, q, 0));
-            __builtin_nontemporal_store(f32x4{sbyte(c, 0) * s, sbyte(c, 1) * s, sbyte(c, 2) * s, sbyte(c, 3) * s},
-                                        (f32x4 *)(out + I8_ELEM(b0, q, 0)));
+            st_decoded<NT>((f32x4 *)(out + I8_ELEM(b0, q, 0)),
+                       f32x4{sbyte(c, 0) * s, sbyte(c, 1) * s, sbyte(c, 2) * s, sbyte(c, 3) * s});
         }
     } else {
 #pragma unroll
@@ -1537,7 +1554,9 @@ hipError_t launch_encode_fp16(const float *x, uint64_t n, uint16_t *codes, hipSt
 }
 
 hipError_t launch_decode_fp16(const uint16_t *codes, uint64_t n, float *out, hipStream_t s) {
-    DEDLOC_LAUNCH(dim3(grid_for(n, (uint64_t)kWG * kVec)), decode_fp16_kernel, s, codes, n, out);
+    const dim3 grid(grid_for(n, (uint64_t)kWG * kVec));
+    if (n >= kNtDecodeFp16) DEDLOC_LAUNCH(grid, decode_fp16_kernel<true>, s, codes, n, out);
+    DEDLOC_LAUNCH(grid, decode_fp16_kernel<false>, s, codes, n, out);
 }
 
 hipError_t launch_encode_i8(const float *x, uint64_t n, int8_t *codes, float *scales, hipStream_t s) {
@@ -1546,7 +1565,9 @@ hipError_t launch_encode_i8(const float *x, uint64_t n, int8_t *codes, float *sc
 
 hipError_t launch_decode_i8(const int8_t *codes, const float *scales, uint64_t n, float *out,
                             hipStream_t s) {
-    DEDLOC_LAUNCH(dim3(grid_for(n, (uint64_t)kI8Block * (kWG / 64))), decode_i8_kernel, s, codes, scales, n, out);
+    const dim3 grid(grid_for(n, (uint64_t)kI8Block * (kWG / 64)));
+    if (n >= kNtDecodeI8) DEDLOC_LAUNCH(grid, decode_i8_kernel<true>, s, codes, scales, n, out);
+    DEDLOC_LAUNCH(grid, decode_i8_kernel<false>, s, codes, scales, n, out);
 }
 
 // Groups of at most this many members take the small peer batch.

@@ -48,3 +48,23 @@ def test_rows(n):
         o = out.cpu().numpy()
         assert np.array_equal(o[:n].view(np.uint16), oracle.encode_fp16(expect / np.float32(8.0)))
         assert np.all(o[n:] == 0x1234) and not np.any(a.cpu().numpy())
+
+
+@pytest.mark.parametrize("n", [(1 << 20) - 1, 1 << 20, (1 << 21) - 1, 1 << 21, (1 << 21) + 2049])
+def test_decode_on_both_sides_of_its_store_rule(n):
+    """The decoders take other stores from 2^20 (fp16) and 2^21
+    (int8) elements on: whole rows and
+    blocks and the partial last ones, bit for bit, nothing past the end."""
+    print(f"\n[decode] {n}", flush=True)
+    rng = np.random.default_rng(n)
+    c16 = rng.integers(0, 0x7C00, n, np.uint16)  # finite, non-negative
+    c8 = rng.integers(-127, 128, n, np.int8)
+    s8 = rng.random((n + 1023) // 1024, np.float32)
+    up = lambda a: torch.from_numpy(a).cuda()
+    for codes, scales, codec, want in (
+            (c16.view(np.int16), None, D.DEDLOC_CODEC_FP16, c16.view(np.float16).astype(np.float32)),
+            (c8, s8, D.DEDLOC_CODEC_I8, c8.astype(np.float32) * np.repeat(s8, 1024)[:n])):
+        back = torch.full((n + 16,), 7.0, device="cuda")
+        D.dedloc_decode(up(codes), None if scales is None else up(scales), n, codec, out=back)
+        got = back.cpu().numpy()
+        assert np.array_equal(got[:n].view(np.uint32), want.view(np.uint32)) and np.all(got[n:] == 7.0)
