@@ -224,14 +224,16 @@ def _peer_ptrs(ts: Sequence, counts, nbytes: int, name: str) -> ctypes.Array:
     """Pointer table of the peers' buffers: a peer with samples must hold
     `nbytes`; a peer without samples is never read (any buffer, or None)."""
     out = []
-    for p, (t, c) in enumerate(zip(ts, counts.tolist())):
+    c = counts.tolist()
+    for p, t in enumerate(ts):
         if t is None:
             out.append(None)
-        elif c == 0 or (t.is_cuda and t.is_contiguous() and t.nbytes >= nbytes):
+        elif c[p] == 0 or (t.is_cuda and t.is_contiguous() and t.nbytes >= nbytes):
             out.append(t.data_ptr())
         else:
             out.append(_dev(t, nbytes, f"{name}[{p}]"))  # raises
-    return (ctypes.c_void_p * len(ts))(*out)
+    # NULL for peers past the end of `ts`: the library has an entry for each count
+    return (ctypes.c_void_p * max(len(ts), len(c)))(*out)
 
 
 @functools.lru_cache(maxsize=None)

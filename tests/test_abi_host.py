@@ -360,3 +360,14 @@ def test_round_call_follows_tables_resized_in_place(monkeypatch):
     bnd.resize(1 << 18, refcheck=False)  # moves
     call()
     assert seen[4][1] == bnd.ctypes.data and seen[4][1] != seen[3][1]
+
+
+def test_peer_tables_and_counts_of_other_lengths():
+    """More scale buffers than peers are refused; of fewer, the missing ones
+    are NULL to the library, which has an entry for each count."""
+    i8, f32 = _FakeTensor(1024, 1), _FakeTensor(1, 4)
+    kw = dict(shard_len=1024, codec=D.DEDLOC_CODEC_I8, out_codes=i8, out_scales=f32)
+    i8.device = "cuda"
+    with pytest.raises(IndexError):
+        D.dedloc_reduce_shard([i8, i8], [1, 2], peer_scales=[f32, f32, f32], **kw)
+    assert list(D._peer_ptrs([f32], np.array([1, 2], np.uint32), 4, "peer_scales")) == [4096, None]
