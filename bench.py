@@ -216,12 +216,14 @@ def _one_pass_held(wl):
     ratio is known (their x' is written by the first pass), or None where the
     round runs as two passes.  The library's rule: enough elements, in
     tensors large enough; at most 2 x 768 units of 4096 elements are held of
-    one tensor."""
+    one tensor, and where the pass averages fp16 messages itself a third of the
+    elements must be."""
     sizes = np.diff(np.asarray(wl.offsets()).astype(np.int64))
     least = 1 << (24 if wl.codec == "fp16" else 23)
     if wl.P < least or wl.P // max(1, int(np.count_nonzero(sizes))) < 1 << 18:
         return None
-    return int(np.minimum(sizes, 2 * 768 * 4096).sum())
+    held = int(np.minimum(sizes, 2 * 768 * 4096).sum())
+    return None if wl.codec == "fp16" and 3 * held < wl.P else held
 
 
 def _instance(kind, dr):

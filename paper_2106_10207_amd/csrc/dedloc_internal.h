@@ -99,14 +99,14 @@ struct ChainArgs {
 };
 
 // A run of consecutive tensors handled by one optimizer launch (it spans
-// fewer than 2^32 elements).  Work items (tiles of one row; units of two
-// in LAMB's one pass) never cross a tensor: tensor k of the chunk covers elements base +
-// [start[k], start[k+1]) and owns items [begin[k], begin[k+1]).
+// fewer than 2^32 elements).  Work items (tiles of one row; units of two in
+// LAMB's one pass) never cross a tensor: tensor k of the chunk covers elements
+// base + [start[k], start[k+1]) and owns items [begin[k], begin[k+1]).
 struct Chunk {
     uint64_t base;                      // absolute offset of the chunk's first element
     uint32_t nt;                        // tensors in this chunk
     uint32_t t0;                        // index of the chunk's first tensor
-    uint32_t row_base;                 // rows of the tensors before the chunk
+    uint32_t row_base;                  // rows of the tensors before the chunk
     uint32_t start[kChunkTensors + 1];  // element offsets relative to base
     uint32_t begin[kChunkTensors + 1];
     uint8_t odd_before[kChunkTensors];  // tensors of the chunk before k with an odd number of rows

@@ -1,5 +1,6 @@
-// gfx950 kernels of libdedloc: wire codecs, the weighted shard average and
-// the two LAMB passes.
+// gfx950 kernels of libdedloc: wire codecs, the weighted shard average, the
+// LAMB and LARS step (LAMB in one pass on large vectors, else two passes) and
+// local accumulation.
 //
 // Every kernel streams HBM in 16-byte vectors per lane; nothing here is a
 // dense contraction, so there is no MFMA.  Compiled with -ffp-contract=off:
@@ -192,7 +193,7 @@ __global__ __launch_bounds__(kWG) void decode_fp16_kernel(const uint16_t *__rest
         for (int h = 0; h < 2; h++) {
             const u32x2 c = *(const u32x2 *)(codes + row + row_at(h));
             st_decoded<NT>((f32x4 *)(out + row + row_at(h)),
-                       f32x4{h2f(c[0] & 0xffffu), h2f(c[0] >> 16), h2f(c[1] & 0xffffu), h2f(c[1] >> 16)});
+                           f32x4{h2f(c[0] & 0xffffu), h2f(c[0] >> 16), h2f(c[1] & 0xffffu), h2f(c[1] >> 16)});
         }
     } else {
         for (uint64_t e = row + threadIdx.x; e < n; e += kWG) out[e] = h2f(codes[e]);
