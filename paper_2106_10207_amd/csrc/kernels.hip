@@ -1165,12 +1165,16 @@ __global__ __launch_bounds__(kWG, kLineGroups) void lamb_a_kernel(const Chunk ch
     auto fetch = [&](const Row<GF> &r) {
         if (r.row >= r.t_hi) return;
         // x plain, m and v and all stores non-temporal: a cache that still holds
-        // part of x from the last call serves it (the same buffers again / three
-        // sets in turn: ALBERT-large's round 204.8 -> 201.7 / 204 -> 205 us, 40M
-        // elements 380 -> 370 / 400 -> 390, the step on 60M 360 -> 352 / 360 -> 352).
-        // With more of them plain the same buffers again gain more and others lose
-        // more: all loads 186 / 221, all 184 / 224, m's loads and stores 193 / 215.
-        r.template load<false>(x, fx);
+        // part of x from the last call serves it (non-temporal / plain; the same
+        // buffers again: 40M elements' round 380 / 370 us, the step on 60M 360 / 352,
+        // ALBERT-large's round alone 191 / 187; three sets in turn: 400 / 390, 360 /
+        // 352, ALBERT-xlarge's round 967 / 959, the step on 17.7M 98.8 / 97.4).  With
+        // more of them plain the same buffers again gain more and others lose more:
+        // ALBERT-large's round with all loads 186 / 221, all 184 / 224, m's loads and
+        // stores 193 / 215.  Beside the local gradient, which is read plainly too,
+        // only the same buffers gain: ALBERT-large 203 / 201, three sets 204.6 / 206.5
+        // (with the gradient non-temporal instead 207 and 210).
+        r.template load<SRC == kSrcPeersFP16Local>(x, fx);
         r.load(m, fm);
         r.load(v, fv);
         if constexpr (!kPeers) fg.load(ga, r);
