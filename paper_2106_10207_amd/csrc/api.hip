@@ -265,6 +265,9 @@ int check_tensors(uint64_t P, const uint64_t *off, uint32_t T) {
 // in 20 49.9 / 55.7, 4M in 200 52 / 41, 17.7M in 25 98 / 123.  Rounds: 9M in 5
 // (int8) 88.0 / 98.6, 9M in 300 138 / 122, 9M in 12 80.8 / 78.6, 12M in one 99.9 /
 // 98.9, 17M in 12 140.6 / 144.8, 20M in 30 162 / 171, 2^30 in 1024 8.9 / 10.1 ms.
+// The mean size is a coarse line: ResNet-50's 161 tensors (159k elements on
+// average, 107 of at most 2048, but most elements in large ones) lie below it and
+// would gain, 32 peers 466 / 494, 16 peers 310 / 334, int8 254 / 278.
 constexpr uint64_t kOnePassElements = 1ull << 23;       // a message or fp32 gradient
 constexpr uint64_t kOnePassElementsPeers = 1ull << 24;  // the fused average
 constexpr uint64_t kOnePassPerTensor = 1ull << 18;
@@ -275,8 +278,9 @@ constexpr uint64_t kOnePassPerTensor = 1ull << 18;
 // on the same buffers, 2, 8, 16 and 60 peers, us: tensors of 12M elements (held
 // 52%) 457 / 475, 574 / 596, 739 / 780, 1078 / 1075; 16.8M (37%) 394 / 397, 493 /
 // 498, 627 / 659, 1021 / 1009; 33M (19%) 277 / 268, 346 / 338, 430 / 441, 1028 /
-// 1010.  A message or fp32 gradient gains throughout (one tensor of 33M 223 / 235,
-// of 2^30 7.8 / 8.2 ms).
+// 1010.  Three sets of buffers in turn, 33M, 4, 8, 16, 32, 41 and 60 peers: 304 /
+// 286, 321 / 316, 449 / 439, 615 / 624, 734 / 740, 971 / 975.  A message or fp32
+// gradient gains throughout (one tensor of 33M 223 / 235, of 2^30 7.8 / 8.2 ms).
 // LARS: x and v of 2^24 elements are 128 MB, half of the Infinity Cache.
 // Non-temporal accesses beyond: 8.5M and 9M elements 61.6 / 65.0 and 75.2 / 78.0
 // us, 12M equal, 18M 148.6 / 141.8, 26M 201.5 / 198.1, 40M 232.5 / 222.5

@@ -344,7 +344,9 @@ __device__ __forceinline__ float reduce_fp16_one(const PeerTable &pt, uint32_t p
 // NT: the gradient's loads carry the non-temporal hint.  Chosen per kernel that
 // calls it, by times per round with the hint / without, three sets of buffers
 // in turn and the same set again and again.  LAMB's pass A, ResNet-50: 32 peers
-// 500 / 503 and 437 / 462 us, 16 peers 335 / 339 and 285 / 305; LARS' pass A,
+// 500 / 503 and 437 / 462 us, 16 peers 335 / 339 and 285 / 305 (three sets: 6M
+// elements in 60 tensors 56.0 / 57.5, 2M in 30 26.0 / 26.1; with few tensors the
+// other way round, 2.8M in 2 33.9 / 32.9, 5M in 3 46.5 / 46.1); LARS' pass A,
 // 32 peers: 415 / 418 and 413 / 399; reduce_fp16_kernel, ALBERT-large's round of
 // 100 peers: 798 / 810 and 783 / 771, ResNet-50's 1220 / 1214 and 1153 / 1177.
 // lamb_a_kernel, which has 4 peer loads in flight and not 16: ALBERT-large, the
