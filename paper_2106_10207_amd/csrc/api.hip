@@ -265,9 +265,10 @@ int check_tensors(uint64_t P, const uint64_t *off, uint32_t T) {
 // in 20 49.9 / 55.7, 4M in 200 52 / 41, 17.7M in 25 98 / 123.  Rounds: 9M in 5
 // (int8) 88.0 / 98.6, 9M in 300 138 / 122, 9M in 12 80.8 / 78.6, 12M in one 99.9 /
 // 98.9, 17M in 12 140.6 / 144.8, 20M in 30 162 / 171, 2^30 in 1024 8.9 / 10.1 ms.
-// The mean size is a coarse line: ResNet-50's 161 tensors (159k elements on
-// average, 107 of at most 2048, but most elements in large ones) lie below it and
-// would gain, 32 peers 466 / 494, 16 peers 310 / 334, int8 254 / 278.
+// The mean size is a coarse line.  ResNet-50's 161 tensors (159k elements on
+// average, 107 of them of at most 2048) lie below it: 32 peers 452 / 442 us on the
+// same buffers and 472 / 464 after a cache flush, but with three sets of buffers
+// in turn 466 / 494, 16 peers 310 / 334, int8 254 / 278.
 constexpr uint64_t kOnePassElements = 1ull << 23;       // a message or fp32 gradient
 constexpr uint64_t kOnePassElementsPeers = 1ull << 24;  // the fused average
 constexpr uint64_t kOnePassPerTensor = 1ull << 18;
