@@ -285,3 +285,29 @@ def test_one_pass_non_finite_gradients():
             assert torch.equal(a.view(torch.int32), b.view(torch.int32))
     finally:
         D.dedloc_test_trust_polls(old)
+
+
+@pytest.mark.parametrize("thirds,extra,one_pass", [(3, 0, True), (3, 8, False), (6, 0, False)])
+def test_fused_average_takes_the_pass_where_the_line_holds_a_third(thirds, extra, one_pass):
+    """One tensor of which the grid's line (two units for each of its workgroups)
+    holds exactly a third, one of eight elements more, and one of which it holds a
+    sixth; the same elements in two tensors take the pass, since it holds a third
+    of each or more.  The workspace's second word tells: the one pass copies the
+    counter into it."""
+    G = 3 * torch.cuda.get_device_properties(0).multi_processor_count
+    n = thirds * 2 * G * 4096 + extra
+    print(f"\n[one pass] fused average of {n}", flush=True)
+    gen = torch.Generator(device=DEV)
+    gen.manual_seed(n)
+    codes = [torch.randn(n, generator=gen, device=DEV).mul_(1e-3).half().view(torch.int16) for _ in range(2)]
+    out = torch.empty(n, dtype=torch.int16, device=DEV)
+    x, m, v = torch.randn(n, device=DEV).mul_(0.02), torch.zeros(n, device=DEV), torch.full((n,), 1e-6, device=DEV)
+    for off, taken in (([0, n], one_pass), ([0, n // 16 * 8, n], True)):
+        off = np.array(off, np.uint64)
+        ws = D.make_workspace(n, off)
+        words = ws.view(torch.int32)
+        words[0], words[1] = 1000, 5
+        D.RoundCall(codes, np.array([1, 2], np.uint32), D.dedloc_partition(n, 2), D.DEDLOC_CODEC_FP16, out, x, m, v, off,
+                    np.full(len(off) - 1, 3, np.uint8), D.lamb_cfg(step=10), ws)()
+        torch.cuda.synchronize()
+        assert (int(words[0]), int(words[1])) == (1001, 1000 if taken else 5)

@@ -107,27 +107,3 @@ def test_two_streams_take_little_longer_than_one():
     two, one = _best_us([apart, together], 5, 3)
     print(f"two streams {two:.0f} us, one {one:.0f} us", flush=True)
     assert two <= 1.7 * one
-
-
-def test_fused_average_of_one_large_tensor():
-    """A round of fp16 messages over one tensor of 2^25 elements, of which the
-    one pass could hold a fifth, takes no longer than over the same elements in
-    tensors small enough for the two passes (measured 268 us with 2 peers; in the
-    one pass 277 to 281)."""
-    print("\n[time] fused average, one large tensor", flush=True)
-    n, peers = 1 << 25, 2
-    gen = torch.Generator(device=DEV)
-    gen.manual_seed(1)
-    codes = [torch.randn(n, generator=gen, device=DEV).mul_(1e-3).half().view(torch.int16) for _ in range(peers)]
-    counts = np.arange(1, peers + 1, dtype=np.uint32)
-    out = torch.empty(n, dtype=torch.int16, device=DEV)
-    x, m, v = torch.randn(n, device=DEV).mul_(0.02), torch.zeros(n, device=DEV), torch.full((n,), 1e-6, device=DEV)
-
-    def call(tensors):
-        off = np.arange(tensors + 1, dtype=np.uint64) * (n // tensors)
-        return D.RoundCall(codes, counts, D.dedloc_partition(n, peers), D.DEDLOC_CODEC_FP16, out, x, m, v, off,
-                           np.full(tensors, 3, np.uint8), D.lamb_cfg(step=10), D.make_workspace(n, off))
-
-    whole, split = _best_us([call(1), call(256)], 9, 5)
-    print(f"one tensor {whole:.0f} us, 256 tensors {split:.0f} us", flush=True)
-    assert whole <= 1.02 * split
